@@ -1549,6 +1549,7 @@ struct Driver {
       ctl->final_err_ref = last_err;
       ctl->converged = converged;
       ctl->dv_last = (float)last_dv;
+      if (p.dv_out) *p.dv_out = (float)last_dv;
     }
   }
 };

@@ -120,12 +120,20 @@ struct KParams {
   const float* cb_vals;     // [groups * 64]
   const int32_t* cb_gptr;   // [blocks + 1]: first group of each block
   int64_t cb_states;        // states per block
+  // resident-value kernel: exchange words [2][n] (cleared per launch), parts per position (log2)
+  unsigned long long* xch;
+  int32_t res_lgp;
+  int32_t pad4;
+  float* dv_out;            // optional: the last sweep's max |dV|
 };
 
 // Workspace layout, shared by the size query and the launches.
 struct WsLayout {
   size_t ctl, unit_count, partial, order, first_mark, vbuf1, ceff, shift, tgt, total;
   size_t zero_bytes;  // prefix cleared before every launch (control + counters)
+  // The resident-value kernel's exchange words uint64[2][n] lie over the first-batch
+  // stamps and the sweep orders, which it does not use; its cleared prefix ends with them.
+  size_t xch, zero_bytes_resident;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -141,9 +149,11 @@ inline WsLayout ws_layout(int32_t storage, int64_t n, int32_t m, int64_t max_uni
   if (storage == kDense) off = align_up(off + (size_t)max_units * sizeof(unsigned int), 256);
   w.first_mark = off; off = align_up(off + 2 * (size_t)n * sizeof(uint32_t), 256);
   w.zero_bytes = off;
+  w.order = off;      off = align_up(off + 3 * (size_t)n * sizeof(int32_t), 256);
+  w.xch = w.first_mark;
+  w.zero_bytes_resident = w.xch + 2 * (size_t)n * sizeof(uint64_t);
   w.partial = off;
   if (storage == kDense) off = align_up(off + (size_t)max_units * (size_t)m * sizeof(float), 256);
-  w.order = off;      off = align_up(off + 3 * (size_t)n * sizeof(int32_t), 256);
   w.vbuf1 = off;      off = align_up(off + (size_t)n * sizeof(float), 256);
   w.ceff = off;       off = align_up(off + (size_t)n * (size_t)m * sizeof(double), 256);
   w.shift = off;      off = align_up(off + (size_t)n * sizeof(double), 256);
@@ -163,14 +173,20 @@ constexpr int kMaxBlocksPerCu = 16;
 
 // Kernel families a launch can run.
 enum Engine : int { kEngineDense = 0, kEngineEll = 1, kEngineBand = 2, kEngineCsr = 3,
-                     kEngineCol = 4 };
+                     kEngineCol = 4, kEngineResident = 5 };
 constexpr int kColThreads = 512;  // threads of a column-block launch (8 wavefronts)
 constexpr int kColRows = 4096;    // rows per column block (the 12-bit row field of a key)
 constexpr int kColGroup = 64;     // entries per group (one per lane of a wavefront)
 
-// Fills p.splits from the grid actually used and launches the persistent
-// kernel cooperatively.  Returns 0 or -1 with a message in err.
-int launch_solve(KParams p, LaunchShape shape, void* stream, char* err, size_t errlen);
+constexpr int kResThreads = 512;      // resident-value kernel: threads at most (256 VGPRs each)
+constexpr int kResMaxStates = 16384;  // resident-value kernel: V of a dense MDP in LDS (64 KB)
+constexpr int kResList = 8192;        // and the states of a workgroup's units of a sweep
+
+// Clears the workspace's prefix (at p.ctl), fills p.splits from the grid
+// actually used and launches the persistent kernel, cooperatively unless one
+// workgroup runs it.  Returns 0 or -1 with a message in err.
+int launch_solve(KParams p, const WsLayout& w, LaunchShape shape, void* stream, char* err,
+                 size_t errlen);
 // The FP64 correction kernel (mbdp_refine.hip) for an FP32 handle; the same
 // contract as launch_solve.
 int launch_refine(KParams p, LaunchShape shape, void* stream, char* err, size_t errlen);
@@ -351,5 +367,11 @@ typedef void (*SolveFn)(KParams);
 SolveFn pick_dense_lp(const KParams& p);
 SolveFn pick_ell_lp(const KParams& p, int units_per_wave_hint);
 SolveFn pick_band_lp(const KParams& p, int units_per_wave_hint);
+// The resident-value kernels of a dense MDP (mbdp_resident*.hip), by the
+// chunk a wavefront requests at a time: 4 rows of at most 2 steps, 4 steps of
+// a row of a cached table, 8 steps of a streamed row (a step is 1 KB).
+enum ResShape : int { kResShort, kResCached, kResStream };
+SolveFn pick_resident(const KParams& p, ResShape shape);
+SolveFn pick_resident_lp(const KParams& p, ResShape shape);
 
 }  // namespace mbdp

@@ -393,6 +393,13 @@ static bool band_fits(const KParams& p, int blocks) {
   return D <= kChunkCap && D + 2 * (int64_t)p.band <= kWinCap && nb <= kBatchCap;
 }
 
+// Largest table kept by the caches between sweeps (the L2s of the eight XCDs
+// and the memory-side cache): read with plain loads; larger ones with
+// non-temporal loads, which left the caches to V and ran 8% faster.
+constexpr int64_t kResCachedBytes = (int64_t)64 << 20;
+constexpr int64_t kResSoloStates = 1024;        // one workgroup: states,
+constexpr int64_t kResSoloBatch = 128 << 10;    // and row bytes of a batch
+
 static int grid_blocks(SolveFn f, const LaunchShape& shape, int* blocks, char* err,
                        size_t errlen) {
   int occ = 0;
@@ -408,9 +415,65 @@ static int grid_blocks(SolveFn f, const LaunchShape& shape, int* blocks, char* e
   return 0;
 }
 
-// The instantiation a launch runs and its grid.
-static int choose(const KParams& p, LaunchShape& shape, SolveFn* fn, int* blocks,
+// The resident-value kernel (mbdp_resident.h) for a dense MDP: V fits in
+// LDS, as do the states of a workgroup's units of a sweep, and the batch's
+// words fit the exchange.  Fills the parts per position and the grid; false
+// where the general dense engine runs.
+static bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blocks) {
+  if (p.storage != kDense || p.n > kResMaxStates) return false;
+  LaunchShape shape = shape0;
+  if (shape.threads > kResThreads) shape.threads = kResThreads;
+  const int64_t wb = p.vdtype == kF32 ? 4 : (p.vdtype == kBF16 ? 2 : 1);
+  if (p.n * wb < 16) return false;  // a row is at least one load
+  const int64_t bytes = p.n * p.m * p.n * wb;
+  // Chunk: short rows side by side; four steps where the caches hold the
+  // table (little latency to cover, few steps wasted past a row's end); eight
+  // otherwise.
+  const int64_t steps = (p.n * wb + 1023) / 1024;
+  const ResShape rs = steps <= 2 ? kResShort
+                      : bytes <= kResCachedBytes ? kResCached
+                                                 : kResStream;
+  SolveFn f = p.vdtype == kF32 ? pick_resident(p, rs) : pick_resident_lp(p, rs);
+  char err[128];
+  int g = 0;
+  if (!f || grid_blocks(f, shape, &g, err, sizeof err) != 0) return false;
+  if (g > shape.cus) g = shape.cus;  // one per CU: the LDS holds one
+  if (g > p.n) g = (int)p.n;
+  const bool policy = p.task == kTaskMPI || (p.task == kTaskSweep && p.policy_sweep);
+  // one workgroup where a batch is so short that the exchange between
+  // workgroups would cost more than its rows
+  const int64_t batch_bytes = p.b * p.m * p.n * wb;
+  if (p.n <= kResSoloStates && batch_bytes <= kResSoloBatch) g = 1;
+  // A position's rows are split into a power of two of parts where that
+  // shortens the longest share of a batch (few positions per workgroup);
+  // an argmin output needs all rows of a state in one place.
+  p.res_lgp = 0;
+  if (g > 1 && !policy && !p.argmin_out) {
+    int64_t best = (p.b + g - 1) / g * p.m;
+    for (int lg = 1; lg <= 6 && (1 << lg) <= p.m; ++lg) {
+      if ((p.b << lg) > p.n) break;
+      const int64_t rows = ((p.b << lg) + g - 1) / g * ((p.m + (1 << lg) - 1) >> lg);
+      if (rows < best) {
+        best = rows;
+        p.res_lgp = lg;
+      }
+    }
+  }
+  const int64_t nb = (p.n + p.b - 1) / p.b;
+  if (nb > 1 && nb * (((p.b << p.res_lgp) + g - 1) / g) > kResList) return false;
+  *fn = f;
+  *blocks = g;
+  shape0 = shape;
+  return true;
+}
+
+// The instantiation a launch runs and its grid.  Fills p.res_lgp.
+static int choose(KParams& p, LaunchShape& shape, SolveFn* fn, int* blocks,
                   int* engine, char* err, size_t errlen) {
+  if (resident_plan(p, shape, fn, blocks)) {
+    *engine = kEngineResident;
+    return 0;
+  }
   // a banded MDP keeps the band-local engine (its V window in LDS beats the
   // column blocks); otherwise, at b = n with column blocks attached, those
   bool band_ok = false;
@@ -462,16 +525,30 @@ static int choose(const KParams& p, LaunchShape& shape, SolveFn* fn, int* blocks
   return grid_blocks(*fn, shape, blocks, err, errlen);
 }
 
-int query_engine(const KParams& p, LaunchShape shape, int* engine, char* err, size_t errlen) {
+int query_engine(const KParams& q, LaunchShape shape, int* engine, char* err, size_t errlen) {
+  KParams p = q;
   SolveFn f = nullptr;
   int blocks = 0;
   return choose(p, shape, &f, &blocks, engine, err, errlen);
 }
 
-int launch_solve(KParams p, LaunchShape shape, void* stream, char* err, size_t errlen) {
+int launch_solve(KParams p, const WsLayout& w, LaunchShape shape, void* stream, char* err,
+                 size_t errlen) {
   SolveFn f = nullptr;
   int blocks = 0, engine = 0;
   if (choose(p, shape, &f, &blocks, &engine, err, errlen) != 0) return -1;
+  if (engine == kEngineResident && blocks == 1) {
+    // no other workgroup to be co-resident with, and the kernel clears its own status words
+    hipLaunchKernelGGL(f, dim3(1), dim3(shape.threads), 0, reinterpret_cast<hipStream_t>(stream), p);
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess) return 0;
+    snprintf(err, errlen, "launch failed: %s", hipGetErrorString(e));
+    return -1;
+  }
+  if (launch_zero(p.ctl, engine == kEngineResident ? w.zero_bytes_resident : w.zero_bytes, stream) != 0) {
+    snprintf(err, errlen, "workspace clear failed: %s", hipGetErrorString(hipGetLastError()));
+    return -1;
+  }
   // dense: split the columns of a state over several workgroups when the
   // batch has fewer states than there are workgroups
   p.splits = 1;

@@ -165,15 +165,13 @@ KParams base_params(const mbdp_mdp* h, void* ws, float* V, int64_t b) {
   p.cb_vals = h->cb_vals;
   p.cb_gptr = h->cb_gptr;
   p.cb_states = h->cb_states;
+  p.xch = reinterpret_cast<unsigned long long*>(base + w.xch);
   return p;
 }
 
-mbdp_status launch(const mbdp_mdp* h, const KParams& p, void* ws, hipStream_t stream) {
-  const WsLayout w = layout(h);
-  if (launch_zero(ws, w.zero_bytes, stream) != 0)
-    return fail(MBDP_ERR_HIP, "workspace clear failed: %s", hipGetErrorString(hipGetLastError()));
+mbdp_status launch(const mbdp_mdp* h, const KParams& p, hipStream_t stream) {
   char err[256] = {0};
-  if (launch_solve(p, shape_of(h), stream, err, sizeof err) != 0)
+  if (launch_solve(p, layout(h), shape_of(h), stream, err, sizeof err) != 0)
     return fail(MBDP_ERR_HIP, "%s", err);
   return MBDP_OK;
 }
@@ -189,7 +187,8 @@ const char* device_error_text(unsigned code) {
 
 // Synchronises and copies the control block back; maps device errors.
 mbdp_status finish(void* ws, hipStream_t stream, Control* out) {
-  MBDP_HIP(hipMemcpyAsync(out, ws, sizeof(Control), hipMemcpyDeviceToHost, stream));
+  // everything but the barrier's arrival slots
+  MBDP_HIP(hipMemcpyAsync(out, ws, offsetof(Control, bar_slots), hipMemcpyDeviceToHost, stream));
   MBDP_HIP(hipStreamSynchronize(stream));
   if (out->error)
     return fail(MBDP_ERR_DEVICE, "device error %u: %s", out->error, device_error_text(out->error));
@@ -424,7 +423,7 @@ mbdp_status mdp_engine(mbdp_mdp_t h, int64_t b, const char** name) {
   int engine = 0;
   char err[256] = {0};
   if (query_engine(p, shape_of(h), &engine, err, sizeof err) != 0) return fail(MBDP_ERR_HIP, "%s", err);
-  static const char* const names[] = {"dense", "ell", "ell-band", "csr", "ell-colblock"};
+  static const char* const names[] = {"dense", "ell", "ell-band", "csr", "ell-colblock", "dense"};
   *name = names[engine];
   return MBDP_OK;
 }
@@ -1038,11 +1037,8 @@ mbdp_status mb_sweep(mbdp_mdp_t h, float* V, const int32_t* policy, int64_t b, u
   p.argmin_out = argmin_out;
   p.seed = seed;
   p.first_sweep = sweep_index;
-  st = launch(h, p, workspace, stream);
-  if (st != MBDP_OK) return st;
-  if (dv_out)
-    MBDP_HIP(hipMemcpyAsync(dv_out, &p.ctl->dv_last, sizeof(float), hipMemcpyDeviceToDevice, stream));
-  return MBDP_OK;
+  p.dv_out = dv_out;
+  return launch(h, p, stream);
 }
 
 mbdp_status mbdp_sync_status(void* workspace, size_t ws_bytes, hipStream_t stream) {
@@ -1088,7 +1084,7 @@ mbdp_status vi_solve_impl(mbdp_mdp_t h, float* V, double* V64_out, int32_t* poli
   p.tgt = reinterpret_cast<double*>(static_cast<char*>(workspace) + w.tgt);
   if (p.recentre_every > 0)
     p.shift = reinterpret_cast<double*>(static_cast<char*>(workspace) + w.shift);
-  st = launch(h, p, workspace, stream);
+  st = launch(h, p, stream);
   if (st != MBDP_OK) return st;
   Control c;
   st = finish(workspace, stream, &c);
@@ -1200,7 +1196,7 @@ mbdp_status mpi_solve(mbdp_mdp_t h, float* V, double* V64_out, int32_t* policy,
   p.tgt = reinterpret_cast<double*>(static_cast<char*>(workspace) + w.tgt);
   if (p.recentre_every > 0)
     p.shift = reinterpret_cast<double*>(static_cast<char*>(workspace) + w.shift);
-  st = launch(h, p, workspace, stream);
+  st = launch(h, p, stream);
   if (st != MBDP_OK) return st;
   Control c;
   st = finish(workspace, stream, &c);
