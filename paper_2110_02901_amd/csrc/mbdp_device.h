@@ -29,14 +29,12 @@ __device__ __forceinline__ uint32_t philox_word0(uint32_t x0, uint32_t x1, uint3
       k0 += 0x9E3779B9u;
       k1 += 0xBB67AE85u;
     }
-    const uint32_t a_hi = __umulhi(0xD2511F53u, x0), a_lo = 0xD2511F53u * x0;
-    const uint32_t b_hi = __umulhi(0xCD9E8D57u, x2), b_lo = 0xCD9E8D57u * x2;
-    const uint32_t y0 = b_hi ^ x1 ^ k0;
-    const uint32_t y2 = a_hi ^ x3 ^ k1;
-    x0 = y0;
-    x1 = b_lo;
-    x2 = y2;
-    x3 = a_lo;
+    // one 64-bit product gives both halves in a single (quarter-rate) instruction
+    const uint64_t a = (uint64_t)0xD2511F53u * x0, b = (uint64_t)0xCD9E8D57u * x2;
+    x0 = (uint32_t)(b >> 32) ^ x1 ^ k0;
+    x1 = (uint32_t)b;
+    x2 = (uint32_t)(a >> 32) ^ x3 ^ k1;
+    x3 = (uint32_t)a;
   }
   return x0;
 }
@@ -155,23 +153,33 @@ __device__ __forceinline__ void wave_argmin_from(double& q, int& a) {
   }
 }
 
-// Order-preserving 64-bit key of a double (monotone in the value).
-__device__ __forceinline__ unsigned long long okey(double x) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-}
-
-__device__ __forceinline__ double okey_value(unsigned long long k) {
-  const unsigned long long u = (k >> 63) ? (k & 0x7FFFFFFFFFFFFFFFull) : ~k;
-  return __longlong_as_double((long long)u);
-}
-
 __device__ __forceinline__ unsigned long long atomic_load_agent(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void atomic_store_agent(unsigned long long* p, unsigned long long v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A value other workgroups read in a later phase, stored through to memory
+// (agent-coherent), and its load past the caches.
+template <class X>
+__device__ __forceinline__ void store_shared(X* p, X v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class X>
+__device__ __forceinline__ X load_shared(const X* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class X>
+__device__ __forceinline__ X load_if_shared(const X* p, bool coherent) {
+  return coherent ? load_shared(p) : *p;
+}
+
+// State at position pos of a batch whose order is `ord`; without one (a batch
+// of all states, inside which the order is free) the position itself.
+__device__ __forceinline__ int32_t state_of(const int32_t* ord, int64_t pos, bool coherent = false) {
+  return ord ? load_if_shared(&ord[pos], coherent) : (int32_t)pos;
 }
 
 // ------------------------------------------------------------ grid barrier
@@ -216,14 +224,29 @@ __device__ __forceinline__ bool wait_at_least(const unsigned long long* word,
   return true;
 }
 
-__device__ __forceinline__ bool grid_sync(GridBarrier& g) {
+//
+// The fences are most of the barrier (256 workgroups of 1024 threads, alone:
+// 6.2 us with both, 4.5 us without the release, 1.8 us without either), so a
+// phase leaves out what it does not need.  `release` false: everything the
+// phase wrote for other workgroups went through agent-coherent stores
+// (atomic_store_agent, store_shared), which are performed device-wide when
+// the wave's vmcnt reaches zero.  `acquire` false: the next phase reads what
+// other workgroups wrote through agent-coherent loads only, which no stale
+// line can answer.
+//
+// reduce_slot >= 0: the barrier ends an epoch whose accumulators the
+// workgroups have published (publish_acc); workgroup 0 reduces them into
+// ctl->acc[reduce_slot] before it releases the barrier, a wavefront per word.
+__device__ __forceinline__ bool grid_sync(GridBarrier& g, bool release = true,
+                                          bool acquire = true, int reduce_slot = -1) {
   __shared__ int s_abort;
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads and stores are done
+  // this wave's loads and stores are done
+  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   g.gen += 1;
   unsigned long long* slots = g.ctl->bar_slots;
   if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     atomic_store_agent(&slots[blockIdx.x], g.gen);
   }
   int ok = 1;
@@ -235,16 +258,36 @@ __device__ __forceinline__ bool grid_sync(GridBarrier& g) {
     // word's store, so each workgroup's acquire below synchronises with all
     // arrivals through workgroup 0 (release -> acquire at agent scope, then
     // the workgroup barrier, then release -> acquire again).
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    // (Without fenced stores there is nothing to relay.)
+    if (release) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
+    if (reduce_slot >= 0 && g.nblocks <= kAccBlocks) {
+      const int lane = threadIdx.x & 63, nw = (int)(blockDim.x >> 6);
+      for (int i = (int)(threadIdx.x >> 6); i < kNumAcc; i += nw) {
+        unsigned long long v = 0;
+        for (unsigned b = (unsigned)lane; b < g.nblocks; b += 64) {
+          const unsigned long long x =
+              atomic_load_agent(&slots[kMaxBlocks / 2 + b * kAccStride + i]);
+          v = i == kAccChanges ? v + x : (x > v ? x : v);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+          const unsigned long long x = __shfl_xor(v, off);
+          v = i == kAccChanges ? v + x : (x > v ? x : v);
+        }
+        if (lane == 0) atomic_store_agent(&g.ctl->acc[reduce_slot][i], v);
+      }
+      __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
     if (threadIdx.x == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (release) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       atomic_store_agent(&g.ctl->bar_release, g.gen);
     }
   }
   if (threadIdx.x == 0) {
     if (ok) ok = wait_at_least(&g.ctl->bar_release, g.gen, g);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (acquire) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (ok) ok = __hip_atomic_load(&g.ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
     s_abort = !ok;
   }

@@ -52,68 +52,89 @@ namespace mbdp {
 // ------------------------------------------------------------ accumulators
 
 // Accumulators of the current epoch: max |dW|, max error against V_ref,
-// max |TW - W|, the range of W and the policy changes.  Two forms with one
+// max |TW - W|, max |W| and the policy changes.  Two forms with one
 // interface.  RegAcc keeps them per thread in registers (committing lanes
 // only) and reduces them at the flush; LdsAcc keeps one copy per workgroup
 // in LDS, updated with LDS atomics, and holds no registers, for the dense
 // engine whose row tiles need every register (it commits few states).
-struct RegAcc {
-  double v[3];  // kAccDv, kAccErr, kAccResid slots below
-  double wmax, wmin;
-  unsigned long long changes;
+//
+// The flush leaves a workgroup's values in its own words of the control
+// block; workgroup 0 reduces them inside the barrier that ends the epoch
+// (grid_sync).  Atomics of all workgroups on one set of words took ~15 us per
+// epoch (3 words x 256 workgroups, ~20 ns each, one after the other), more
+// than a whole sweep of 16 384 states.
+__device__ __forceinline__ void publish_acc(Control* ctl, int slot,
+                                            const unsigned long long (&v)[kNumAcc]) {
+  if (gridDim.x <= kAccBlocks) {
+    unsigned long long* mine = ctl->bar_slots + kMaxBlocks / 2 + blockIdx.x * kAccStride;
+#pragma unroll
+    for (int i = 0; i < kNumAcc; ++i) atomic_store_agent(&mine[i], v[i]);
+    return;
+  }
+  unsigned long long* acc = ctl->acc[slot];
+#pragma unroll
+  for (int i = 0; i < kNumAcc; ++i) {
+    if (v[i] == 0) continue;
+    if (i == kAccChanges)
+      atomicAdd(&acc[i], v[i]);
+    else
+      atomicMax(&acc[i], v[i]);
+  }
+}
 
-  __device__ __forceinline__ static int idx(int i) { return i == kAccDv ? 0 : (i == kAccErr ? 1 : 2); }
+struct RegAcc {
+  double v[3];  // kAccDv, kAccErr, kAccResid
+  unsigned wabs;  // bits of max |W| (FP32)
+  unsigned changes;
+
   __device__ __forceinline__ void init() {
     v[0] = v[1] = v[2] = 0.0;
-    wmax = -INFINITY;
-    wmin = INFINITY;
+    wabs = 0;
     changes = 0;
   }
-  __device__ __forceinline__ void max_abs(int i, double x) { v[idx(i)] = fmax(v[idx(i)], x); }
-  __device__ __forceinline__ void range(double w) {
-    wmax = fmax(wmax, w);
-    wmin = fmin(wmin, w);
+  __device__ __forceinline__ void max_abs(int i, double x) { v[i] = fmax(v[i], x); }
+  __device__ __forceinline__ void range(float w) {
+    wabs = max(wabs, __float_as_uint(w) & 0x7FFFFFFFu);
   }
   __device__ __forceinline__ void count_change() { changes += 1; }
 
-  // Merges the workgroup's values into epoch slot `slot` and clears them.
-  // Every thread of the workgroup must call it.
-  __device__ __forceinline__ void flush(Control* ctl, int slot) {
-    __shared__ double sh[16][5];
-    __shared__ unsigned long long shc[16];
+  // The workgroup's values to its words of epoch slot `slot`, and clears them.
+  // Every thread of the workgroup must call it.  `improve`: an improvement
+  // pass (residual, changes), else a sweep (change, range, error with vref).
+  __device__ __forceinline__ void flush(Control* ctl, int slot, bool improve, bool vref) {
+    __shared__ unsigned long long sh[16][kNumAcc];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const double dv = wave_max_d(v[0]), err = wave_max_d(v[1]), res = wave_max_d(v[2]);
-    const double hi = wave_max_d(wmax), lo = wave_min_d(wmin);
-    unsigned long long ch = changes;
+    double dv = 0.0, err = 0.0, res = 0.0;
+    unsigned wa = 0, ch = 0;
+    if (improve) {
+      res = wave_max_d(v[kAccResid]);
+      ch = changes;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) ch += __shfl_xor(ch, off);
+      for (int off = 32; off > 0; off >>= 1) ch += __shfl_xor(ch, off);
+    } else {
+      dv = wave_max_d(v[kAccDv]);
+      wa = wabs;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) wa = max(wa, (unsigned)__shfl_xor((int)wa, off));
+    }
+    if (vref) err = wave_max_d(v[kAccErr]);
     if (lane == 0) {
-      sh[w][0] = dv;
-      sh[w][1] = err;
-      sh[w][2] = res;
-      sh[w][3] = hi;
-      sh[w][4] = lo;
-      shc[w] = ch;
+      sh[w][kAccDv] = (unsigned long long)__double_as_longlong(dv);
+      sh[w][kAccErr] = (unsigned long long)__double_as_longlong(err);
+      sh[w][kAccResid] = (unsigned long long)__double_as_longlong(res);
+      sh[w][kAccWabs] = (unsigned long long)__double_as_longlong((double)__uint_as_float(wa));
+      sh[w][kAccChanges] = ch;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-      double a = sh[0][0], b = sh[0][1], c = sh[0][2], d = sh[0][3], e = sh[0][4];
-      unsigned long long f = shc[0];
-      for (int i = 1; i < nw; ++i) {
-        a = fmax(a, sh[i][0]);
-        b = fmax(b, sh[i][1]);
-        c = fmax(c, sh[i][2]);
-        d = fmax(d, sh[i][3]);
-        e = fmin(e, sh[i][4]);
-        f += shc[i];
+      unsigned long long a[kNumAcc];
+#pragma unroll
+      for (int i = 0; i < kNumAcc; ++i) {
+        a[i] = sh[0][i];
+        for (int x = 1; x < nw; ++x)
+          a[i] = i == kAccChanges ? a[i] + sh[x][i] : (sh[x][i] > a[i] ? sh[x][i] : a[i]);
       }
-      unsigned long long* acc = ctl->acc[slot];
-      if (a > 0.0) atomicMax(&acc[kAccDv], (unsigned long long)__double_as_longlong(a));
-      if (b > 0.0) atomicMax(&acc[kAccErr], (unsigned long long)__double_as_longlong(b));
-      if (c > 0.0) atomicMax(&acc[kAccResid], (unsigned long long)__double_as_longlong(c));
-      if (d > -INFINITY) atomicMax(&acc[kAccWmax], okey(d));
-      if (e < INFINITY) atomicMin(&acc[kAccWmin], okey(e));
-      if (f) atomicAdd(&acc[kAccChanges], f);
+      publish_acc(ctl, slot, a);
     }
     __syncthreads();
     init();
@@ -121,45 +142,39 @@ struct RegAcc {
 };
 
 struct LdsAcc {
-  unsigned long long* a;  // [kNumAcc]: doubles >= 0 as bits, the W range as ordered keys
+  unsigned long long* a;  // [kNumAcc]
 
   __device__ __forceinline__ void init() {
     __shared__ unsigned long long acc[kNumAcc];
     a = acc;
     if (threadIdx.x == 0)  // visible after the next barrier, before any commit
-      for (int i = 0; i < kNumAcc; ++i) a[i] = (i == kAccWmin) ? ~0ull : 0ull;
+      for (int i = 0; i < kNumAcc; ++i) a[i] = 0ull;
   }
   __device__ __forceinline__ void max_abs(int i, double x) {  // NaN is ignored, as by fmax
     if (x == x) atomicMax(&a[i], (unsigned long long)__double_as_longlong(x));
   }
-  __device__ __forceinline__ void range(double w) {
-    atomicMax(&a[kAccWmax], okey(w));
-    atomicMin(&a[kAccWmin], okey(w));
+  __device__ __forceinline__ void range(float w) {
+    atomicMax(&a[kAccWabs], (unsigned long long)__double_as_longlong((double)fabsf(w)));
   }
   __device__ __forceinline__ void count_change() { atomicAdd(&a[kAccChanges], 1ull); }
 
-  __device__ __forceinline__ void flush(Control* ctl, int slot) {
+  __device__ __forceinline__ void flush(Control* ctl, int slot, bool, bool) {
     __syncthreads();
     if (threadIdx.x == 0) {
-      unsigned long long* acc = ctl->acc[slot];
-      if (a[kAccDv]) atomicMax(&acc[kAccDv], a[kAccDv]);
-      if (a[kAccErr]) atomicMax(&acc[kAccErr], a[kAccErr]);
-      if (a[kAccResid]) atomicMax(&acc[kAccResid], a[kAccResid]);
-      if (a[kAccWmax]) atomicMax(&acc[kAccWmax], a[kAccWmax]);
-      if (a[kAccWmin] != ~0ull) atomicMin(&acc[kAccWmin], a[kAccWmin]);
-      if (a[kAccChanges]) atomicAdd(&acc[kAccChanges], a[kAccChanges]);
-      for (int i = 0; i < kNumAcc; ++i) a[i] = (i == kAccWmin) ? ~0ull : 0ull;
+      unsigned long long v[kNumAcc];
+#pragma unroll
+      for (int i = 0; i < kNumAcc; ++i) {
+        v[i] = a[i];
+        a[i] = 0ull;
+      }
+      publish_acc(ctl, slot, v);
     }
     __syncthreads();
   }
 };
 
 __device__ __forceinline__ void reset_slot(Control* ctl, int slot) {
-  for (int i = 0; i < kNumAcc; ++i) {
-    unsigned long long v = 0ull;
-    if (i == kAccWmin) v = ~0ull;
-    atomic_store_agent(&ctl->acc[slot][i], v);
-  }
+  for (int i = 0; i < kNumAcc; ++i) atomic_store_agent(&ctl->acc[slot][i], 0ull);
 }
 
 __device__ __forceinline__ double slot_double(Control* ctl, int slot, int i) {
@@ -215,11 +230,11 @@ template <class Acc>
 __device__ __forceinline__ void commit_sweep(const KParams& p, const Ctx& c, int32_t s, double q,
                                              int a, float old, double aux, Acc& L) {
   const float w = (float)q;
-  c.wr[s] = w;
+  store_shared(&c.wr[s], w);
   if (p.argmin_out) p.argmin_out[s] = a;
   L.max_abs(kAccDv, fabs((double)w - (double)old));
   if (p.vref) L.max_abs(kAccErr, fabs((double)w - aux));
-  L.range((double)w);
+  L.range(w);
 }
 
 // Policy improvement of state s (Algorithm 1): V is not written.
@@ -227,7 +242,7 @@ template <class Acc>
 __device__ __forceinline__ void commit_improve(const KParams& p, int32_t s, double q, int a,
                                                float old, bool count, double aux, Acc& L) {
   if (count && (int)aux != a) L.count_change();
-  p.policy[s] = a;
+  store_shared(&p.policy[s], a);
   L.max_abs(kAccResid, fabs(q - (double)old));
 }
 
@@ -258,8 +273,10 @@ struct ValF32 {
   static constexpr int kType = kF32;
   static constexpr int kBytes = 4;
   // ELL entries e .. e+3 (e a multiple of 4)
+  template <bool NT>
   __device__ __forceinline__ static f4 ell4(const KParams& p, size_t e) {
-    return __builtin_nontemporal_load(reinterpret_cast<const f4*>(p.val + e));
+    const f4* q = reinterpret_cast<const f4*>(p.val + e);
+    return NT ? __builtin_nontemporal_load(q) : *q;
   }
   __device__ __forceinline__ static float scale(const KParams&, int64_t) { return 1.f; }
   __device__ __forceinline__ static float dense_at(const KParams& p, size_t i) {
@@ -270,9 +287,10 @@ struct ValF32 {
 struct ValBF16 {
   static constexpr int kType = kBF16;
   static constexpr int kBytes = 2;
+  template <bool NT>
   __device__ __forceinline__ static f4 ell4(const KParams& p, size_t e) {
-    const u2 w = __builtin_nontemporal_load(
-        reinterpret_cast<const u2*>(static_cast<const uint16_t*>(p.pq) + e));
+    const u2* q = reinterpret_cast<const u2*>(static_cast<const uint16_t*>(p.pq) + e);
+    const u2 w = NT ? __builtin_nontemporal_load(q) : *q;
     return f4{bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
   }
   __device__ __forceinline__ static float scale(const KParams& p, int64_t row) {
@@ -292,9 +310,10 @@ struct ValBF16 {
 struct ValFP8 {
   static constexpr int kType = kFP8;
   static constexpr int kBytes = 1;
+  template <bool NT>
   __device__ __forceinline__ static f4 ell4(const KParams& p, size_t e) {
-    return fp8x4(__builtin_nontemporal_load(
-        reinterpret_cast<const unsigned*>(static_cast<const uint8_t*>(p.pq) + e)));
+    const unsigned* q = reinterpret_cast<const unsigned*>(static_cast<const uint8_t*>(p.pq) + e);
+    return fp8x4(NT ? __builtin_nontemporal_load(q) : *q);
   }
   __device__ __forceinline__ static float scale(const KParams& p, int64_t row) {
     return p.rscale[row];
@@ -452,6 +471,8 @@ constexpr int kMaxActions = 1024;
 template <int R, int VEC, class T = ValF32>
 struct DenseEngine {
   static constexpr bool kBand = false;
+  static constexpr bool kPlainStores = true, kCoherent = false;  // (of the split counters)
+  __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
   using Acc = LdsAcc;
   // 16-byte row loads in flight per thread and step: 16 for FP32 and BF16;
   // 8 for FP8, whose tiles also hold 16 values of V per load
@@ -532,7 +553,7 @@ struct DenseEngine {
       if constexpr (IDENT)
         s = (int32_t)i;
       else
-        s = ord[i];
+        s = state_of(ord, i);
       // the state is uniform over each wave: keep it (and the row bases) scalar
       s = __builtin_amdgcn_readfirstlane(s);
       uint32_t j0, j1;
@@ -666,6 +687,35 @@ struct DenseEngine {
   }
 };
 
+// ------------------------------------------------------------ V in LDS
+//
+// Sparse MDPs of at most kLdsStates states: every workgroup copies V into LDS
+// at the start of a phase (agent-coherent loads, 64 KB at most), so the
+// gathers are LDS reads and the barriers need neither fence.
+constexpr int kLdsStates = 16384;
+
+__device__ __forceinline__ float* lds_values() {
+  __shared__ float v[kLdsStates] __attribute__((aligned(16)));
+  return v;
+}
+
+__device__ __forceinline__ const float* stage_values(const float* rd, int64_t n) {
+  float* v = lds_values();
+  const int pairs = (int)(n >> 1);  // V buffers are at least 8-byte aligned where rd % 8 == 0
+  if (((uintptr_t)rd & 7) == 0) {
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(rd);
+#pragma unroll 8
+    for (int i = (int)threadIdx.x; i < pairs; i += (int)blockDim.x)
+      reinterpret_cast<unsigned long long*>(v)[i] = load_shared(src + i);
+    if ((n & 1) && threadIdx.x == 0) v[n - 1] = load_shared(rd + n - 1);
+  } else {
+#pragma unroll 4
+    for (int i = (int)threadIdx.x; i < (int)n; i += (int)blockDim.x) v[i] = load_shared(rd + i);
+  }
+  __syncthreads();
+  return v;
+}
+
 // ------------------------------------------------------------ ELL engine
 //
 // Constant row length k, k % 4 == 0, k <= 256.  A row is served by LPR =
@@ -674,9 +724,12 @@ struct DenseEngine {
 // time; in the policy mode each lane group serves its own state.  LPR is a
 // template parameter so that the lane reductions unroll with constant
 // shuffle offsets.
-template <int UNR, int LPR, class T = ValF32>
+// LDSV: V is read from LDS, the table (small then) with plain loads.
+template <int UNR, int LPR, class T = ValF32, bool LDSV = false>
 struct EllEngine {
   static constexpr bool kBand = false;
+  static constexpr bool kPlainStores = false, kCoherent = LDSV;
+  __device__ __forceinline__ static bool coherent(const KParams&, int) { return LDSV; }
   using Acc = RegAcc;
 
 
@@ -713,10 +766,14 @@ struct EllEngine {
       if constexpr (IDENT)
         v = (int32_t)pc;
       else
-        v = ord[pc];
+        v = state_of(ord, pc, LDSV);
       return valid ? v : -1;
     };
-    const float* __restrict__ rd = c.rd;
+    const float* rd;
+    if constexpr (LDSV)
+      rd = stage_values(c.rd, p.n);
+    else
+      rd = c.rd;
     int32_t s_next[UNR];
 #pragma unroll
     for (int x = 0; x < UNR; ++x) s_next[x] = state_at(gw, x);
@@ -739,15 +796,16 @@ struct EllEngine {
         float scl[UNR];
 #pragma unroll
         for (int x = 0; x < UNR; ++x) {
-          int av = p.policy[sc[x]];
+          int av = load_if_shared(&p.policy[sc[x]], LDSV);
           if (av < 0 || av >= m) {
             if (s[x] >= 0) raise_abort(p.ctl, kDevBadPolicy);
             av = 0;
           }
           a[x] = av;
           const size_t e = ((size_t)sc[x] * m + av) * (size_t)k + (size_t)lcol;
-          cc[x] = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
-          vv[x] = T::ell4(p, e);
+          cc[x] = LDSV ? *reinterpret_cast<const i4*>(p.col + e)
+                       : __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
+          vv[x] = T::template ell4<!LDSV>(p, e);
           cost[x] = cost_of<CE>(p, (int64_t)sc[x] * m + av);
           scl[x] = T::scale(p, (int64_t)sc[x] * m + av);
         }
@@ -791,8 +849,9 @@ struct EllEngine {
 #pragma unroll
         for (int x = 0; x < UNR; ++x) {
           const size_t e = ((size_t)sc[x] * m + ac) * (size_t)k + (size_t)lcol;
-          cc[x] = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
-          vv[x] = T::ell4(p, e);
+          cc[x] = LDSV ? *reinterpret_cast<const i4*>(p.col + e)
+                       : __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
+          vv[x] = T::template ell4<!LDSV>(p, e);
           cost[x] = cost_of<CE>(p, (int64_t)sc[x] * m + ac);
           scl[x] = T::scale(p, (int64_t)sc[x] * m + ac);
         }
@@ -856,7 +915,7 @@ struct EllEngine {
         if (a < m && lane_has_data) {
           const size_t e = ((size_t)s * m + a) * (size_t)k + (size_t)l * 4;
           const i4 cc = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
-          const f4 vv = T::ell4(p, e);
+          const f4 vv = T::template ell4<true>(p, e);
           part = (double)vv.x * p.shift[cc.x] + (double)vv.y * p.shift[cc.y] +
                  (double)vv.z * p.shift[cc.z] + (double)vv.w * p.shift[cc.w];
         }
@@ -1012,7 +1071,7 @@ struct BandEngine : EllEngine<UNR, LPR, T> {
         if constexpr (IDENT)
           o = pc;
         else
-          o = (int)lst[pc];
+          o = lst ? (int)lst[pc] : pc;
         sc[x] = (int32_t)bg.c0 + o;
         s[x] = valid ? sc[x] : -1;
         old[x] = at(sc[x]);
@@ -1034,7 +1093,7 @@ struct BandEngine : EllEngine<UNR, LPR, T> {
           a[x] = av;
           const size_t e = ((size_t)sc[x] * m + av) * (size_t)k + (size_t)lcol;
           cc[x] = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
-          vv[x] = T::ell4(p, e);
+          vv[x] = T::template ell4<true>(p, e);
           cost[x] = cost_of<CE>(p, (int64_t)sc[x] * m + av);
           scl[x] = T::scale(p, (int64_t)sc[x] * m + av);
         }
@@ -1073,7 +1132,7 @@ struct BandEngine : EllEngine<UNR, LPR, T> {
         for (int x = 0; x < UNR; ++x) {
           const size_t e = ((size_t)sc[x] * m + ac) * (size_t)k + (size_t)lcol;
           cc[x] = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p.col + e));
-          vv[x] = T::ell4(p, e);
+          vv[x] = T::template ell4<true>(p, e);
           cost[x] = cost_of<CE>(p, (int64_t)sc[x] * m + ac);
           scl[x] = T::scale(p, (int64_t)sc[x] * m + ac);
         }
@@ -1238,55 +1297,196 @@ struct ColEngine : EllEngine<UNR, LPR, ValF32> {
 
 // ------------------------------------------------------------ general CSR engine
 
+// Rows of any length.  The rows of a workgroup's states (its positions of the
+// batch, every gridDim-th) go to groups of LPG lanes, kRows rows of a group at
+// a time, so that the chain row pointer -> column and value -> V(column) of
+// one row is not waited for alone; LPG is about half the mean row length.
+// Each row's Q goes to LDS, then a thread per state takes the minimum and
+// commits.  Bound by the chain of dependent loads (order, policy, row pointer,
+// column, V) and the barrier.  MPI at n = 50 000, m = 5, rows of 1 to 40
+// entries, b = 5000: 49.5 -> 22.5 ms against a wavefront per state with its
+// rows one after the other, fenced barriers and the order drawn per batch;
+// forward and backward of J* at n = 16 384, m = 8, k = 64 (b = n, V in LDS on both
+// paths) 70.5 -> 43.3 ms.
+constexpr int kCsrRows = 1024;  // Q values of a round in LDS
+
+struct CsrShared {
+  double q[kCsrRows];
+  int32_t s[kCsrRows], a[kCsrRows];
+};
+
+__device__ __forceinline__ CsrShared& csr_shared() {
+  __shared__ CsrShared sh;
+  return sh;
+}
+
+// Sum over groups of LPG lanes.
+template <int LPG>
+__device__ __forceinline__ float lane_group_sum(float v) {
+#pragma unroll
+  for (int off = LPG >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+template <int LPG, bool LDSV = false>
 struct CsrEngine {
   static constexpr bool kBand = false;
+  static constexpr bool kPlainStores = false, kCoherent = true;
   using Acc = RegAcc;
+  static constexpr int kRows = 4;  // rows of a group in flight
+  static constexpr int kEnt = 2;   // entries of a row per lane and pass
+
+  // Small batches gather V past the caches, so that their barriers need no
+  // L2 invalidation (2.7 us); large ones gather more than the memory side
+  // serves in that time.
+  __device__ __forceinline__ static bool coherent(const KParams& p, int mode) {
+    if (LDSV) return true;
+    const double rows = (double)p.b * (mode == kModePolicy ? 1.0 : (double)p.m);
+    return rows * (double)p.nnz <= 524288.0 * (double)p.n * (double)p.m;
+  }
 
   template <bool CE, bool IDENT, class Acc>
   __device__ __forceinline__ static void batch(const KParams& p, const int32_t* ord, int64_t bk,
                                                const Ctx& c, int mode, Acc& L) {
-    const int m = p.m;
-    const int lane = threadIdx.x & 63;
-    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-    const bool improve = mode >= kModeImprove;
-    for (int64_t u = gw; u < bk; u += nw) {
-      int32_t s;
-      if constexpr (IDENT)
-        s = (int32_t)u;
-      else
-        s = ord[u];
-      const float old = c.rd[s];
-      const double aux = commit_aux<CE, IDENT>(p, s);
-      double qb = INFINITY;
-      int ab = 0x7fffffff;
-      int a_lo = mode == kModePolicy ? p.policy[s] : 0;
-      if (a_lo < 0 || a_lo >= m) {
-        if (lane == 0) raise_abort(p.ctl, kDevBadPolicy);
-        a_lo = 0;
-      }
-      const int a_hi = mode == kModePolicy ? a_lo + 1 : m;
-      for (int a = a_lo; a < a_hi; ++a) {
-        const int64_t row = (int64_t)s * m + a;
-        const int64_t e0 = p.row_ptr[row], e1 = p.row_ptr[row + 1];
-        float part = 0.f;
-        for (int64_t e = e0 + lane; e < e1; e += kWave)
-          part = fmaf(__builtin_nontemporal_load(p.val + e), c.rd[p.col[e]], part);
-        part = wave_sum(part);
-        const double q = cost_of<CE>(p, row) + p.gamma * (double)part;
-        if (q < qb) {
-          qb = q;
-          ab = a;
+    if constexpr (LDSV)
+      run<CE, IDENT, true>(p, ord, bk, c, mode, L);
+    else if (!IDENT && coherent(p, mode))
+      run<CE, IDENT, true>(p, ord, bk, c, mode, L);
+    else
+      run<CE, IDENT, false>(p, ord, bk, c, mode, L);
+  }
+
+  template <bool COH>
+  __device__ __forceinline__ static float value(const float* rd, int32_t j) {
+    if constexpr (LDSV)
+      return rd[j];
+    else
+      return load_if_shared(&rd[j], COH);
+  }
+
+  template <bool CE, bool IDENT, bool COH, class Acc>
+  __device__ __forceinline__ static void run(const KParams& p, const int32_t* ord, int64_t bk,
+                                             const Ctx& c, int mode, Acc& L) {
+    CsrShared& sh = csr_shared();
+    const bool pol = mode == kModePolicy, improve = mode >= kModeImprove;
+    const int m = p.m, tid = (int)threadIdx.x;
+    const int mr = pol ? 1 : m;                     // rows of a state
+    const int piece = min(mr, kCsrRows);            // rows of a state per round
+    const int per_round = kCsrRows / piece;         // states per round
+    const int64_t mine = blockIdx.x < bk ? (bk - blockIdx.x + gridDim.x - 1) / gridDim.x : 0;
+    const int group = tid / LPG, l = tid % LPG, groups = (int)blockDim.x / LPG;
+    const float* rd;
+    if constexpr (LDSV)
+      rd = stage_values(c.rd, p.n);
+    else
+      rd = c.rd;
+    for (int64_t j0 = 0; j0 < mine; j0 += per_round) {
+      const int ns = (int)min((int64_t)per_round, mine - j0);
+      // (a state per thread: per_round <= kCsrRows, a multiple of the threads is looped)
+      for (int i = tid; i < ns; i += (int)blockDim.x) {
+        const int64_t pos = blockIdx.x + (j0 + i) * gridDim.x;
+        int32_t s;
+        if constexpr (IDENT)
+          s = (int32_t)pos;
+        else
+          s = state_of(ord, pos, COH);
+        int a = 0;
+        if (pol) {
+          a = load_if_shared(&p.policy[s], COH);
+          if (a < 0 || a >= m) {
+            raise_abort(p.ctl, kDevBadPolicy);
+            a = 0;
+          }
         }
+        sh.s[i] = s;
+        sh.a[i] = a;
       }
-      if (ab == 0x7fffffff) ab = a_lo;
-      consume(aux);
-      if (lane == 0) {
+      __syncthreads();
+      double best = INFINITY;
+      int besta = 0;  // of state `tid` (one state per round where a state has more than kCsrRows rows)
+      for (int a0 = 0; a0 < mr; a0 += piece) {
+        const int pr = min(piece, mr - a0), nr = ns * pr;
+        for (int r0 = group; r0 < nr; r0 += groups * kRows) {
+          int64_t e0[kRows], e1[kRows];
+          double cost[kRows];
+          float part[kRows];
+#pragma unroll
+          for (int q = 0; q < kRows; ++q) {
+            const int r = min(r0 + q * groups, nr - 1);
+            const int i = r / pr;
+            const int64_t row = (int64_t)sh.s[i] * m + sh.a[i] + a0 + (r - i * pr);
+            e0[q] = p.row_ptr[row] + l;
+            e1[q] = p.row_ptr[row + 1];
+            cost[q] = cost_of<CE>(p, row);
+            part[q] = 0.f;
+          }
+          bool more = true;
+          while (more) {
+            int32_t cc[kRows][kEnt];
+            float vv[kRows][kEnt];
+#pragma unroll
+            for (int q = 0; q < kRows; ++q)
+#pragma unroll
+              for (int u = 0; u < kEnt; ++u) {
+                const int64_t e = e0[q] + u * LPG;
+                cc[q][u] = e < e1[q] ? p.col[e] : -1;
+                vv[q][u] = e < e1[q] ? p.val[e] : 0.f;
+              }
+            float gv[kRows][kEnt];
+#pragma unroll
+            for (int q = 0; q < kRows; ++q)
+#pragma unroll
+              for (int u = 0; u < kEnt; ++u)
+                gv[q][u] = cc[q][u] >= 0 ? value<COH>(rd, cc[q][u]) : 0.f;
+            more = false;
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+#pragma unroll
+              for (int u = 0; u < kEnt; ++u) part[q] = fmaf(vv[q][u], gv[q][u], part[q]);
+              e0[q] += kEnt * LPG;
+              more = more || e0[q] < e1[q];
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < kRows; ++q) {
+            const float sum = lane_group_sum<LPG>(part[q]);
+            const int r = r0 + q * groups;
+            if (l == 0 && r < nr) sh.q[r] = cost[q] + p.gamma * (double)sum;
+          }
+        }
+        __syncthreads();
+        if (tid < ns && piece < mr) {  // a state of several rounds (ns = 1)
+          for (int r = 0; r < pr; ++r)
+            if (sh.q[r] < best) {
+              best = sh.q[r];
+              besta = a0 + r;
+            }
+        }
+        if (piece < mr) __syncthreads();  // sh.q is written again
+      }
+      for (int i = tid; i < ns; i += (int)blockDim.x) {
+        const int32_t s = sh.s[i];
+        const float old = value<COH>(rd, s);
+        const double aux = commit_aux<CE, IDENT>(p, s);
+        double qb = best;
+        int ab = besta;
+        if (piece == mr) {
+          qb = INFINITY;
+          ab = sh.a[i];
+          for (int r = 0; r < mr; ++r) {  // ascending actions: strictly smaller keeps the lowest
+            const double q = sh.q[i * mr + r];
+            if (q < qb) {
+              qb = q;
+              ab = pol ? sh.a[i] : r;
+            }
+          }
+        }
         if (improve)
           commit_improve(p, s, qb, ab, old, mode == kModeImproveCount, aux, L);
         else
           commit_sweep(p, c, s, qb, ab, old, aux, L);
       }
+      __syncthreads();
     }
   }
 
@@ -1325,6 +1525,12 @@ struct Driver {
   int64_t prev_count;     // states of the previous batch still to copy forward
   unsigned epoch;         // sweeps + improvement passes, selects accumulator slot
   int64_t gtid, gthreads;
+  // This thread's place in the order and copy loops: runs of 16 elements go
+  // round the workgroups.  With consecutive threads on consecutive elements
+  // a batch of a few thousand positions was the work of a few workgroups,
+  // all of whose wavefronts evaluated the Feistel network (~25 us) while
+  // the other workgroups waited at the barrier.
+  int64_t spread;
   // band-local engine: this workgroup's part of the previous batch, a run of
   // list buffer band_prev_buf (-1: none yet)
   int band_prev_buf, band_prev_lo, band_prev_hi;
@@ -1348,6 +1554,7 @@ struct Driver {
     epoch = 0;
     gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     gthreads = (int64_t)gridDim.x * blockDim.x;
+    spread = ((int64_t)(threadIdx.x >> 4) * gridDim.x + blockIdx.x) * 16 + (threadIdx.x & 15);
     band_prev_buf = -1;
     band_prev_lo = band_prev_hi = 0;
   }
@@ -1358,30 +1565,33 @@ struct Driver {
     return v ? v : 1u;
   }
 
-  // order[t % 3][pos] for pos in [begin, begin + count): sigma_t or perm.
-  // The states of a sweep's first batch (begin == 0) are stamped.
-  __device__ __forceinline__ void fill_order(uint64_t t, int64_t begin, int64_t count) {
+  // order[t % 3][.]: sigma_t or perm.  The states of the first batch are
+  // stamped.  (A whole sweep at a time, during the first batch of the sweep
+  // before: the network's latency, ~3 us with the cycle walk, is then paid once
+  // per sweep instead of once per batch.)
+  __device__ __forceinline__ void fill_order(uint64_t t) {
+    const int64_t count = p.n, b = p.b;
+    if (b >= count && !p.perm) return;  // one batch: the order inside it is free
     int32_t* dst = p.order + (size_t)(t % 3) * (size_t)p.n;
-    const bool first = begin == 0;
     const uint32_t st = stamp(t);
     uint32_t* mark = p.first_mark + (size_t)(t & 1) * (size_t)p.n;
     if (p.perm) {
-      for (int64_t i = gtid; i < count; i += gthreads) {
-        int32_t v = p.perm[begin + i];
+      for (int64_t i = spread; i < count; i += gthreads) {
+        int32_t v = p.perm[i];
         if (v < 0 || (int64_t)v >= p.n) {
           raise_abort(p.ctl, kDevBadPerm);
           v = 0;
         }
-        dst[begin + i] = v;
-        if (first) mark[v] = st;
+        store_shared(&dst[i], v);
+        if (i < b) store_shared(&mark[v], st);
       }
       return;
     }
     const OrderKey key = make_order_key(p.n, p.seed, t);
-    for (int64_t i = gtid; i < count; i += gthreads) {
-      const int32_t v = (int32_t)sweep_order_at((uint32_t)(begin + i), key);
-      dst[begin + i] = v;
-      if (first) mark[v] = st;
+    for (int64_t i = spread; i < count; i += gthreads) {
+      const int32_t v = (int32_t)sweep_order_at((uint32_t)i, key);
+      store_shared(&dst[i], v);
+      if (i < b) store_shared(&mark[v], st);
     }
   }
 
@@ -1395,6 +1605,10 @@ struct Driver {
   __device__ __forceinline__ bool sweep(uint64_t t, int mode) {
     if constexpr (Eng::kBand) return sweep_band<Eng, CE>(t, mode);
     const int64_t n = p.n, b = p.b, nb = (n + b - 1) / b;
+    // a coherent engine's sweeps read what others wrote past the caches: no
+    // barrier acquires (an improvement pass, which may read V through them,
+    // does that itself)
+    const bool coh = Eng::coherent(p, mode);
     if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, (int)((epoch + 1) % 3));
     const int32_t* ord = p.order + (size_t)(t % 3) * (size_t)n;
     for (int64_t k = 0; k < nb; ++k) {
@@ -1404,19 +1618,20 @@ struct Driver {
       // (only possible for the first batch, whose states are stamped)
       const uint32_t st = stamp(t);
       const uint32_t* mark = p.first_mark + (size_t)(t & 1) * (size_t)n;
-      for (int64_t i = gtid; i < prev_count; i += gthreads) {
-        const int32_t s = prev_order[i];
-        if (k != 0 || mark[s] != st) c.wr[s] = c.rd[s];
+      for (int64_t i = spread; i < prev_count; i += gthreads) {
+        const int32_t s = load_if_shared(&prev_order[i], coh);
+        if (k != 0 || load_if_shared(&mark[s], coh) != st)
+          store_shared(&c.wr[s], load_if_shared(&c.rd[s], coh));
       }
-      if (k + 1 < nb)
-        fill_order(t, kb + b, min(b, n - kb - b));
-      else
-        fill_order(t + 1, 0, min(b, n));
-      Eng::template batch<CE, false>(p, ord + kb, bk, c, mode, L);
-      prev_order = ord + kb;
-      prev_count = bk;
-      if (k == nb - 1) L.flush(p.ctl, slot());
-      if (!grid_sync(g)) return false;
+      if (k == 0 && p.task != kTaskSweep) fill_order(t + 1);
+      // one batch of all states: no order, nothing to copy forward
+      const int32_t* bord = nb == 1 && !p.perm ? nullptr : ord + kb;
+      Eng::template batch<CE, false>(p, bord, bk, c, mode, L);
+      prev_order = bord;
+      prev_count = bord ? bk : 0;
+      const bool end = k == nb - 1;
+      if (end) L.flush(p.ctl, slot(), false, p.vref != nullptr);
+      if (!grid_sync(g, Eng::kPlainStores, !coh, end ? slot() : -1)) return false;
       ++phase;
     }
     ++epoch;
@@ -1434,26 +1649,33 @@ struct Driver {
     const int nb = (int)((p.n + p.b - 1) / p.b);
     const int buf = (int)(t & 1);
     if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, (int)((epoch + 1) % 3));
-    band_sort(p, sh, bg, t, buf, nb);
+    // one batch of all states: no order, nothing to copy forward
+    const bool one = nb == 1;
+    if (!one) band_sort(p, sh, bg, t, buf, nb);
     for (int k = 0; k < nb; ++k) {
       Ctx c{rd_buf(), wr_buf()};
-      for (int i = threadIdx.x; i < bg.wn; i += blockDim.x) sh.win[i] = c.rd[bg.wlo + i];
+      for (int i = threadIdx.x; i < bg.wn; i += blockDim.x)
+        sh.win[i] = load_shared(&c.rd[bg.wlo + i]);
       __syncthreads();
       if (band_prev_buf >= 0) {
         const uint16_t* prev = sh.lst[band_prev_buf];
         for (int i = band_prev_lo + (int)threadIdx.x; i < band_prev_hi; i += blockDim.x) {
           const int o = prev[i];
           if (k == 0 && ((sh.first0[o >> 5] >> (o & 31)) & 1u)) continue;
-          c.wr[bg.c0 + o] = sh.win[bg.c0 + o - bg.wlo];
+          store_shared(&c.wr[bg.c0 + o], sh.win[bg.c0 + o - bg.wlo]);
         }
       }
-      const int lo = sh.off[k], hi = sh.off[k + 1];
-      Eng::template batch_band<CE, false>(p, sh, sh.lst[buf] + lo, hi - lo, bg, c, mode, L);
-      band_prev_buf = buf;
+      const int lo = one ? 0 : sh.off[k], hi = one ? bg.dw : sh.off[k + 1];
+      Eng::template batch_band<CE, false>(p, sh, one ? nullptr : sh.lst[buf] + lo, hi - lo, bg, c,
+                                          mode, L);
+      band_prev_buf = one ? -1 : buf;
       band_prev_lo = lo;
       band_prev_hi = hi;
-      if (k == nb - 1) L.flush(p.ctl, slot());
-      if (!grid_sync(g)) return false;
+      const bool end = k == nb - 1;
+      if (end) L.flush(p.ctl, slot(), false, p.vref != nullptr);
+      // V is read through the window only (agent-coherent loads), the policy
+      // by the workgroup that wrote it
+      if (!grid_sync(g, false, false, end ? slot() : -1)) return false;
       ++phase;
     }
     ++epoch;
@@ -1466,12 +1688,13 @@ struct Driver {
     const BandGeom bg = band_geom(p);
     if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, (int)((epoch + 1) % 3));
     Ctx c{rd_buf(), wr_buf()};
-    for (int i = threadIdx.x; i < bg.wn; i += blockDim.x) sh.win[i] = c.rd[bg.wlo + i];
+    for (int i = threadIdx.x; i < bg.wn; i += blockDim.x)
+      sh.win[i] = load_shared(&c.rd[bg.wlo + i]);
     __syncthreads();
     Eng::template batch_band<CE, true>(p, sh, nullptr, bg.dw, bg, c,
                                        count ? kModeImproveCount : kModeImprove, L);
-    L.flush(p.ctl, slot());
-    if (!grid_sync(g)) return false;
+    L.flush(p.ctl, slot(), true, p.vref != nullptr);
+    if (!grid_sync(g, false, false, slot())) return false;
     ++epoch;
     return true;
   }
@@ -1480,10 +1703,14 @@ struct Driver {
   __device__ __forceinline__ bool improve(bool count) {
     if constexpr (Eng::kBand) return improve_band<Eng, CE>(count);
     if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, (int)((epoch + 1) % 3));
+    if constexpr (Eng::kCoherent) {
+      if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      __syncthreads();
+    }
     CtxT<VT> c{rd_buf(), wr_buf()};
     Eng::template batch<CE, true>(p, nullptr, p.n, c, count ? kModeImproveCount : kModeImprove, L);
-    L.flush(p.ctl, slot());
-    if (!grid_sync(g)) return false;
+    L.flush(p.ctl, slot(), true, p.vref != nullptr);
+    if (!grid_sync(g, Eng::kPlainStores, true, slot())) return false;
     ++epoch;
     return true;
   }
@@ -1499,7 +1726,7 @@ struct Driver {
   __device__ __forceinline__ bool recentre(long long& count) {
     const float* cur = rd_buf();
     for (int64_t s = gtid; s < p.n; s += gthreads) {
-      const double r = p.shift[s] + (double)cur[s];
+      const double r = p.shift[s] + (double)load_shared(&cur[s]);
       p.shift[s] = r;
       if (p.vref) p.tgt[s] = p.vref[s] - r;
       buf0[s] = 0.f;
@@ -1515,9 +1742,7 @@ struct Driver {
   // last sweep changed W by less than 2^-14 of its magnitude.
   __device__ __forceinline__ bool want_recentre(int slot_, double last_dv, long long since) const {
     if (p.recentre_every <= 0 || since < p.recentre_every) return false;
-    const double wmax = okey_value(atomic_load_agent(&p.ctl->acc[slot_][kAccWmax]));
-    const double wmin = okey_value(atomic_load_agent(&p.ctl->acc[slot_][kAccWmin]));
-    const double wabs = fmax(fabs(wmax), fabs(wmin));
+    const double wabs = slot_double(p.ctl, slot_, kAccWabs);
     if (!isfinite(wabs) || wabs <= 0.0) return false;
     return p.recentre_force || wabs > 16384.0 * last_dv;
   }
@@ -1529,15 +1754,15 @@ struct Driver {
     const float* cur = rd_buf();
     if (p.shift) {
       for (int64_t s = gtid; s < p.n; s += gthreads) {
-        const double v = (double)cur[s] + p.shift[s];
+        const double v = (double)load_shared(&cur[s]) + p.shift[s];
         p.vbuf0[s] = (float)v;
         if (p.v64_out) p.v64_out[s] = v;
       }
     } else {
       if (cur != p.vbuf0)
-        for (int64_t s = gtid; s < p.n; s += gthreads) p.vbuf0[s] = cur[s];
+        for (int64_t s = gtid; s < p.n; s += gthreads) p.vbuf0[s] = load_shared(&cur[s]);
       if (p.v64_out)
-        for (int64_t s = gtid; s < p.n; s += gthreads) p.v64_out[s] = (double)cur[s];
+        for (int64_t s = gtid; s < p.n; s += gthreads) p.v64_out[s] = (double)load_shared(&cur[s]);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       Control* ctl = p.ctl;
@@ -1584,7 +1809,7 @@ solve_kernel(KParams p) {
     for (int64_t i = d.gtid; i < n * p.m; i += d.gthreads) p.ceff[i] = (double)p.c32[i];
   }
   long long since_recentre = 0;
-  if constexpr (!Eng::kBand) d.fill_order(t, 0, min(p.b, n));
+  if constexpr (!Eng::kBand) d.fill_order(t);
   if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, 0);
   if (!grid_sync(d.g)) return;
 

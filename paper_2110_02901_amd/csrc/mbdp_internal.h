@@ -20,20 +20,22 @@ enum DeviceError : uint32_t {
   kDevBadPolicy = 3,      // policy entry outside [0, m)
 };
 
-// Accumulators of one epoch (a sweep or an improvement pass).  Doubles are
-// kept as order-preserving 64-bit keys so that atomic max/min on unsigned
-// integers give the max/min of the values.
+// Accumulators of one epoch (a sweep or an improvement pass): the bits of
+// non-negative doubles, whose order is that of the values, and a count.
 enum Acc : int {
-  kAccDv = 0,      // max |W_new - W_old| (non-negative double bits)
+  kAccDv = 0,      // max |W_new - W_old|
   kAccErr = 1,     // max |W_new + r - V_ref|
-  kAccWmax = 2,    // max W_new (ordered key)
-  kAccWmin = 3,    // min W_new (ordered key)
+  kAccResid = 2,   // max |TW - W|
+  kAccWabs = 3,    // max |W_new| (a NaN counts as larger than any value)
   kAccChanges = 4, // policy changes (count)
-  kAccResid = 5,   // max |TW - W| (non-negative double bits)
-  kNumAcc = 6
+  kNumAcc = 5
 };
 
 constexpr int kMaxBlocks = 4096;  // persistent workgroups per launch (arrival slots)
+// Grids of at most kAccBlocks workgroups use only the first arrival slots;
+// the others then hold each workgroup's accumulators of the epoch.
+constexpr int kAccBlocks = 256;
+constexpr int kAccStride = 8;     // words per workgroup, from slot kMaxBlocks / 2 on
 
 struct alignas(256) Control {
   unsigned long long bar_release;  // last barrier generation released by workgroup 0
@@ -41,7 +43,7 @@ struct alignas(256) Control {
   unsigned int abort;            // nonzero: every workgroup leaves
   unsigned int error;            // DeviceError
   unsigned long long pad1[31];
-  unsigned long long acc[3][16]; // rotating epoch accumulators, kNumAcc used
+  unsigned long long acc[3][16]; // rotating epoch accumulators, kNumAcc used (reduced)
   // results written by workgroup 0 at the end of a launch
   long long sweeps;
   long long outer_iters;
@@ -67,6 +69,7 @@ struct KParams {
   double gamma;
   const float* P;          // dense [n][m][n] (FP32 storage)
   const int64_t* row_ptr;  // CSR
+  int64_t nnz;
   const int32_t* col;
   const float* val;
   int32_t ell_k;           // constant row length (kEll), else 0

@@ -341,6 +341,17 @@ static SolveFn pick(const KParams& p, int units_per_wave_hint) {
     int lpr = 1;
     while (lpr * 4 < p.ell_k) lpr <<= 1;
     const bool two = units_per_wave_hint >= 2;
+    if (p.n <= kLdsStates) {  // V in LDS; one state per wavefront iteration fills the chip
+      switch (lpr) {
+        case 1: return solve_fn<EllEngine<1, 1, ValF32, true>>(p.task);
+        case 2: return solve_fn<EllEngine<1, 2, ValF32, true>>(p.task);
+        case 4: return solve_fn<EllEngine<1, 4, ValF32, true>>(p.task);
+        case 8: return solve_fn<EllEngine<1, 8, ValF32, true>>(p.task);
+        case 16: return solve_fn<EllEngine<1, 16, ValF32, true>>(p.task);
+        case 32: return solve_fn<EllEngine<1, 32, ValF32, true>>(p.task);
+        default: return solve_fn<EllEngine<1, 64, ValF32, true>>(p.task);
+      }
+    }
     switch (lpr) {
       case 1: return two ? solve_fn<EllEngine<2, 1>>(p.task) : solve_fn<EllEngine<1, 1>>(p.task);
       case 2: return two ? solve_fn<EllEngine<2, 2>>(p.task) : solve_fn<EllEngine<1, 2>>(p.task);
@@ -351,7 +362,18 @@ static SolveFn pick(const KParams& p, int units_per_wave_hint) {
       default: return two ? solve_fn<EllEngine<2, 64>>(p.task) : solve_fn<EllEngine<1, 64>>(p.task);
     }
   }
-  return solve_fn<CsrEngine>(p.task);
+  // lanes per row: about half the mean row length (rounded to a power of two)
+  const int64_t len = p.nnz / (p.n * p.m);
+  if (p.n <= kLdsStates) {
+    if (len <= 10) return solve_fn<CsrEngine<4, true>>(p.task);
+    if (len <= 28) return solve_fn<CsrEngine<8, true>>(p.task);
+    if (len <= 100) return solve_fn<CsrEngine<32, true>>(p.task);
+    return solve_fn<CsrEngine<64, true>>(p.task);
+  }
+  if (len <= 10) return solve_fn<CsrEngine<4>>(p.task);
+  if (len <= 28) return solve_fn<CsrEngine<8>>(p.task);
+  if (len <= 100) return solve_fn<CsrEngine<32>>(p.task);
+  return solve_fn<CsrEngine<64>>(p.task);
 }
 
 // The band-local instantiation for ELL rows of LPR <= 16 lanes, or null.

@@ -41,7 +41,7 @@ namespace {
 template <class Acc>
 __device__ __forceinline__ void commit64(const KParams& p, const CtxT<double>& c, int32_t s,
                                          double q, int a, double old, Acc& L) {
-  c.wr[s] = q;
+  store_shared(&c.wr[s], q);
   if (p.argmin_out) p.argmin_out[s] = a;
   L.max_abs(kAccDv, fabs(q - old));
   if (p.vref) L.max_abs(kAccErr, fabs(q - p.vref[s]));
@@ -54,7 +54,7 @@ __device__ __forceinline__ void improve64(const KParams& p, int32_t s, double q,
                                           double old, bool count, Acc& L) {
   if (p.policy) {
     if (count && p.policy[s] != a) L.count_change();
-    p.policy[s] = a;
+    store_shared(&p.policy[s], a);
   }
   L.max_abs(kAccResid, fabs(q - old));
   if (p.vref) L.max_abs(kAccErr, fabs(old - p.vref[s]));
@@ -100,6 +100,8 @@ __device__ __forceinline__ Dense64Shared& dense64_shared() {
 template <int VEC>
 struct Dense64Engine {
   static constexpr bool kBand = false;
+  static constexpr bool kPlainStores = false, kCoherent = false;
+  __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
   using Acc = LdsAcc;
   static constexpr int R = 8;   // rows of a state per pass
   static constexpr int U = 1;   // column steps in flight (R * U 16-byte loads per thread)
@@ -173,7 +175,7 @@ struct Dense64Engine {
       if constexpr (IDENT)
         s = (int32_t)i;
       else
-        s = ord[i];
+        s = state_of(ord, i);
       s = __builtin_amdgcn_readfirstlane(s);
       for (int a0 = 0; a0 < m; a0 += R) {
         const int nrows = min(R, m - a0);
@@ -223,7 +225,7 @@ struct Dense64Engine {
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int64_t nwv = (int64_t)gridDim.x * (blockDim.x >> 6);
     for (int64_t i = gw; i < bk; i += nwv) {
-      const int32_t s = __builtin_amdgcn_readfirstlane(ord[i]);
+      const int32_t s = __builtin_amdgcn_readfirstlane(state_of(ord, i));
       int a = __builtin_amdgcn_readfirstlane(p.policy[s]);
       if (a < 0 || a >= m) {
         if (lane == 0) raise_abort(p.ctl, kDevBadPolicy);
@@ -299,6 +301,8 @@ struct Dense64Engine {
 template <int LPR>
 struct Ell64Engine {
   static constexpr bool kBand = false;
+  static constexpr bool kPlainStores = false, kCoherent = false;
+  __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
   using Acc = RegAcc;
   static constexpr int kRpp = kWave / LPR;  // rows per wavefront pass
 
@@ -333,7 +337,7 @@ struct Ell64Engine {
       for (int64_t u = gw; u * kRpp < bk; u += nwv) {
         const int64_t pos = u * kRpp + g;
         const bool valid = pos < bk;
-        const int32_t s = ord[valid ? pos : 0];
+        const int32_t s = state_of(ord, valid ? pos : 0);
         int a = p.policy[s];
         if (a < 0 || a >= m) {
           if (valid) raise_abort(p.ctl, kDevBadPolicy);
@@ -350,7 +354,7 @@ struct Ell64Engine {
       if constexpr (IDENT)
         s = (int32_t)u;
       else
-        s = ord[u];
+        s = state_of(ord, u);
       double qb = INFINITY;
       int ab = 0x7fffffff;
       for (int a0 = 0; a0 < m; a0 += kRpp) {
@@ -380,6 +384,8 @@ struct Ell64Engine {
 
 struct Csr64Engine {
   static constexpr bool kBand = false;
+  static constexpr bool kPlainStores = false, kCoherent = false;
+  __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
   using Acc = RegAcc;
 
   __device__ __forceinline__ static double row_dot(const KParams& p, int64_t row,
@@ -404,7 +410,7 @@ struct Csr64Engine {
       if constexpr (IDENT)
         s = (int32_t)u;
       else
-        s = ord[u];
+        s = state_of(ord, u);
       s = __builtin_amdgcn_readfirstlane(s);
       if (mode == kModePolicy) {
         int a = __builtin_amdgcn_readfirstlane(p.policy[s]);
@@ -447,7 +453,7 @@ refine_kernel(KParams p) {
   const double gamma = p.gamma, inv = 1.0 / (1.0 - gamma);
   uint64_t t = p.first_sweep;
   for (int64_t s = d.gtid; s < n; s += d.gthreads) p.vd1[s] = p.vd0[s];
-  d.fill_order(t, 0, min(p.b, n));
+  d.fill_order(t);
   if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, 0);
   if (!grid_sync(d.g)) return;
 

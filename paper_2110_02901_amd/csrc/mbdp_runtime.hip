@@ -142,6 +142,7 @@ KParams base_params(const mbdp_mdp* h, void* ws, float* V, int64_t b) {
   p.gamma = h->gamma;
   p.P = h->P;
   p.row_ptr = h->row_ptr;
+  p.nnz = h->nnz;
   p.col = h->col;
   p.val = h->val;
   p.ell_k = h->ell_k;
