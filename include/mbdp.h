@@ -201,7 +201,7 @@ typedef struct {
   uint64_t seed;          /* sweep orders sigma_t of this MDP */
   double* V;              /* device [n]: V0 in, the last iterate out */
   int32_t* policy;        /* device [n]: greedy policy at the last iterate, or NULL */
-  int32_t lanes;          /* lanes per state: 16, 32 or 64; 0 picks by row length */
+  int32_t lanes;          /* lanes per state: 16, 32 or 64; 0 picks by team size */
   int32_t team;           /* workgroups serving the MDP, 1..16; 0 picks by work */
 } mbdp_batch_item;
 

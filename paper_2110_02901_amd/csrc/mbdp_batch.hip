@@ -8,20 +8,21 @@
 // and accumulated in FP64, so no re-centring is needed.  The launch is an
 // ordinary one (no cooperative launch) and can be captured in a hipGraph.
 //
-// The heaviest MDPs (bytes per sweep times the sweeps gamma asks for) are
-// served by a team of workgroups instead, so that one long solve does not
-// hold the whole launch on one compute unit: the members split each batch's
-// states, publish the new values in a global buffer, meet at a team barrier
-// (an arrival counter), and each copies the batch into its own LDS V.  The
+// Heavy MDPs are served by a team of workgroups instead, so that one long
+// solve does not hold the whole launch on one compute unit: the members
+// split each batch's states, store the new values through to memory, meet
+// at an arrival counter, and each copies the batch into its own LDS V.  The
 // queue hands out the teams' tickets first and the host keeps the members of
 // all teams within the compute units of the device, so every member of every
 // team is resident from the start and no member waits for a workgroup that
 // is busy with another MDP.
 //
-// A lane group of LANES lanes serves one state at a time: lanes split the
-// row's columns, 16 bytes of the row per lane and step, and the rows of the
-// state are taken 8 (FP8: 4) at a time so the V values a lane loads from
-// LDS serve all of them.
+// Bound: the rows (a compute unit alone reads 35 to 47 GB/s of BF16 / FP32
+// rows, above its 25 GB/s share of HBM), for FP8 the conversions to FP64
+// (9 GB/s), in teams the meeting of each batch (~10 us of 36 at 13 members).
+// 96 BF16 MDPs of 256 to 2048 states, m = 8: 546 -> 194 ms against one state
+// after the other per lane group, each waiting for its own order, rows, costs
+// and sums.
 
 #include <hip/hip_runtime.h>
 
@@ -95,300 +96,405 @@ __device__ __forceinline__ MBDP_GLOBAL T* gview_mut(void* p) {
 
 struct BatchShared {
   double V[kBatchMaxN];
-  double newv[kBatchMaxB];
-  int32_t sidx[kBatchMaxB];
+  double newv[kBatchMaxB];            // a lone workgroup's new values of the batch
+  uint16_t order[2][kBatchMaxN];      // sigma_t, by sweep parity
   double red[16];
   int item, rank, ok;
 };
 
-// min_a Q(s, a) (FP64) and its action, lowest index on ties, for the lane
-// group of `sl` (lane within the group) serving state s.  Every lane of the
-// group returns the same result.
+__device__ __forceinline__ BatchShared& batch_shared() {
+  __shared__ BatchShared sh;
+  return sh;
+}
+
+// LDS-only workgroup barrier: row loads in flight stay in flight.
+__device__ __forceinline__ void batch_lds_barrier() {
+  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// MB-VI on one MDP by a team of K >= 1 workgroups; `rank` is this one's.
+//
+// A lane group of LANES lanes serves one state at a time.  Its work is a
+// sequence of chunks: R rows of the state by one step of LANES * 16 bytes of
+// each row.  Two chunk buffers are in flight in turn, across states and, since
+// rows do not depend on V, across batches: the first two chunks of the next
+// batch are requested before the batch is committed.  Every chunk issues the
+// same loads (rows past m and columns past ld are moved to valid ones and
+// dropped), so that the wait for one chunk leaves the other in flight.
+// The order of a sweep is drawn once, by all threads, into LDS; drawing it
+// per state on every lane cost ~2 us per state, and waiting for each state's
+// rows, costs and reductions in turn held a workgroup to 12-20 GB/s.
 template <int VT, int LANES>
-__device__ __forceinline__ void batch_state(const BatchItem& I, const double* V, int32_t s,
-                                            int sl, double& qbest, int& abest) {
+struct BatchSolver {
   using B = BatchVals<VT>;
-  constexpr int EPL = B::kEpl;
-  constexpr int kBatchRows = batch_rows<VT>();
-  const int64_t m = I.m, ld = I.ld;
-  const MBDP_GLOBAL uint8_t* P = gview<uint8_t>(I.P);
-  const MBDP_GLOBAL float* C = gview<float>(I.c);
-  const MBDP_GLOBAL float* RS = gview<float>(I.rscale);
-  qbest = INFINITY;
-  abest = 0;
-  for (int a0 = 0; a0 < m; a0 += kBatchRows) {
-    double acc[kBatchRows];
-#pragma unroll
-    for (int r = 0; r < kBatchRows; ++r) acc[r] = 0.0;
-    const size_t row0 = (size_t)s * m + a0;
-    for (int64_t j = (int64_t)sl * EPL; j < ld; j += (int64_t)LANES * EPL) {
-      double v[EPL];
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) v[e] = V[j + e];
-      u4 x[kBatchRows];
-#pragma unroll
-      for (int r = 0; r < kBatchRows; ++r)
-        x[r] = (a0 + r < m) ? __builtin_nontemporal_load((const MBDP_GLOBAL u4*)(
-                                  P + ((row0 + r) * (size_t)ld + (size_t)j) * B::kBytes))
-                            : u4{0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int r = 0; r < kBatchRows; ++r) {
-        double d[EPL];
-        B::decode(x[r], d);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[r] = fma(d[e], v[e], acc[r]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kBatchRows; ++r) {
-#pragma unroll
-      for (int off = LANES >> 1; off > 0; off >>= 1) acc[r] += __shfl_xor(acc[r], off);
-      const int a = a0 + r;
-      if (a < m) {
-        const size_t row = row0 + r;
-        const double scale = VT == kF32 ? 1.0 : (double)RS[row];
-        const double q = (double)C[row] + I.gamma * (scale * acc[r]);
-        if (q < qbest) {  // strictly smaller keeps the lowest action on ties
-          qbest = q;
-          abest = a;
-        }
-      }
-    }
-  }
-}
+  static constexpr int EPL = B::kEpl;
+  static constexpr int R = batch_rows<VT>();
+  static constexpr int GPW = kWave / LANES;  // lane groups per wavefront
 
-template <int VT, int LANES>
-__device__ void batch_solve_item(const BatchItem& I, BatchShared& sh, BatchStat* stats,
-                                 double tol, long long max_sweeps) {
-  constexpr int GPW = kWave / LANES;  // lane groups per wave
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sl = lane % LANES;
-  const int group = wave * GPW + lane / LANES;
-  const int groups = (blockDim.x >> 6) * GPW;
-  const int64_t n = I.n, b = I.b, nb = (n + b - 1) / b;
-  const MBDP_GLOBAL double* V0 = gview<double>(I.V);
-  for (int64_t j = threadIdx.x; j < I.ld; j += blockDim.x) sh.V[j] = j < n ? V0[j] : 0.0;
-  __syncthreads();
-  const unsigned long long t_start = wall_clock64();
-  long long sweeps = 0;
-  double dv = INFINITY;
-  int converged = 0;
-  for (uint64_t t = 0; (long long)t < max_sweeps; ++t) {
-    const OrderKey key = make_order_key(n, I.seed, t);
-    double dvl = 0.0;
-    for (int64_t k = 0; k < nb; ++k) {
-      const int64_t kb = k * b, bk = min(b, n - kb);
-      for (int64_t i = group; i < bk; i += groups) {
-        const int32_t s = (int32_t)sweep_order_at((uint32_t)(kb + i), key);
-        double q;
-        int a;
-        batch_state<VT, LANES>(I, sh.V, s, sl, q, a);
-        if (sl == 0) {
-          sh.newv[i] = q;
-          sh.sidx[i] = s;
-          dvl = fmax(dvl, fabs(q - sh.V[s]));
-        }
-      }
-      __syncthreads();  // every state of the batch read the values before it
-      for (int64_t i = threadIdx.x; i < bk; i += blockDim.x) sh.V[sh.sidx[i]] = sh.newv[i];
-      __syncthreads();  // committed before the next batch reads
-    }
-    ++sweeps;
-    dvl = wave_max_d(dvl);
-    if (lane == 0) sh.red[wave] = dvl;
-    __syncthreads();
-    dv = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) dv = fmax(dv, sh.red[w]);
-    __syncthreads();
-    if (dv <= tol) {
-      converged = 1;
-      break;
-    }
-  }
-  // results: V, and the greedy policy at the final V
-  MBDP_GLOBAL double* Vout = gview_mut<double>(I.V);
-  for (int64_t j = threadIdx.x; j < n; j += blockDim.x) Vout[j] = sh.V[j];
-  if (I.policy) {
-    MBDP_GLOBAL int32_t* pol = gview_mut<int32_t>(I.policy);
-    for (int64_t s = group; s < n; s += groups) {
-      double q;
-      int a;
-      batch_state<VT, LANES>(I, sh.V, (int32_t)s, sl, q, a);
-      if (sl == 0) pol[s] = a;
-    }
-  }
-  if (threadIdx.x == 0) {
-    BatchStat st;
-    st.sweeps = sweeps;
-    st.dv = dv;
-    st.converged = converged;
-    st.pad = 0;
-    st.t_start = t_start;
-    st.t_end = wall_clock64();
-    stats[I.index] = st;
-  }
-  __syncthreads();
-}
+  struct Buf {
+    u4 x[R];
+    float cost, scale;  // of row row_of_lane()
+  };
 
-// Team of K workgroups on one MDP (see the file comment).  The arrival
-// counter only grows: the p-th barrier of the solve (p = 0, 1, ...) ends when
-// it reaches (p + 1) K.  Release by one thread after every wave's memory
-// operations are done makes the workgroup's writes visible device-wide;
-// acquire after the wait makes the others' writes visible to it.  Gives up
-// (false, and raises the launch's abort flag) after `timeout` ticks or when
-// another team gave up.
-__device__ __forceinline__ bool team_sync(unsigned long long* arrive, unsigned* abort,
-                                          unsigned long long target,
-                                          unsigned long long timeout, BatchShared& sh) {
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads and stores are done
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  const BatchItem* it;
+  BatchShared& sh;
+  const BatchArgs& A;
+  const MBDP_GLOBAL uint8_t* P;
+  const MBDP_GLOBAL float* C;
+  const MBDP_GLOBAL float* RS;
+  double gamma;
+  int lane, wave, nw, sl, gid, gstride;
+  int n, m, ld, nsteps, nc, K;   // steps per row, chunks per state, workgroups
+  Buf a, b;
+  bool have;
+
+  __device__ __forceinline__ BatchSolver(const BatchItem* item, int rank, BatchShared& s,
+                                         const BatchArgs& args)
+      : it(item), sh(s), A(args) {
+    const BatchItem& I = *item;
+    P = gview<uint8_t>(I.P);
+    C = gview<float>(I.c);
+    RS = gview<float>(I.rscale);
+    gamma = I.gamma;
+    K = I.team;
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    nw = (int)(blockDim.x >> 6);
+    sl = lane % LANES;
+    gid = (rank * nw + wave) * GPW + lane / LANES;
+    gstride = K * nw * GPW;
+    n = (int)I.n;
+    m = I.m;
+    ld = (int)I.ld;
+    nsteps = (ld + LANES * EPL - 1) / (LANES * EPL);
+    nc = nsteps * ((m + R - 1) / R);
+    have = false;
+    for (int r = 0; r < R; ++r) a.x[r] = b.x[r] = u4{0u, 0u, 0u, 0u};
+    a.cost = a.scale = b.cost = b.scale = 0.f;
+  }
+
+  // After the halving reduction lane sl holds row row_of_lane() of the chunk.
+  __device__ __forceinline__ int row_of_lane() const {
+    return sl / (LANES / R);
+  }
+
+  // Chunk c of the t-th state of this lane group's positions kb + gid + t gstride < kb + bk.
+  __device__ __forceinline__ int state_at(const uint16_t* ord, int kb, int bk, int t) const {
+    const int pos = min(gid + t * gstride, bk - 1);
+    return ord ? (int)ord[kb + pos] : kb + pos;
+  }
+
+  __device__ __forceinline__ void load(int s, int pass, int st, Buf& f) const {
+    const int j = min((st * LANES + sl) * EPL, ld - EPL);
+    const MBDP_GLOBAL uint8_t* p0 = P + ((size_t)s * m * (size_t)ld + (size_t)j) * B::kBytes;
+    const size_t rb = (size_t)ld * B::kBytes;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      f.x[r] = __builtin_nontemporal_load(
+          (const MBDP_GLOBAL u4*)(p0 + (size_t)min(pass * R + r, m - 1) * rb));
+    const size_t row = (size_t)s * m + min(pass * R + row_of_lane(), m - 1);
+    f.cost = C[row];
+    if constexpr (VT != kF32) f.scale = RS[row];
+  }
+
+  __device__ __forceinline__ void consume(int st, const Buf& f, double (&acc)[R]) const {
+    const int j = (st * LANES + sl) * EPL;
+    const bool in = j < ld;
+    const double* vp = sh.V + (in ? j : 0);
+    double v[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) v[e] = vp[e];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double d[EPL];
+      B::decode(in ? f.x[r] : u4{0u, 0u, 0u, 0u}, d);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[r] = fma(d[e], v[e], acc[r]);
+    }
+  }
+
+  // Sums over the lane group of the R accumulators, one row per lane: each
+  // step halves the rows a lane keeps, then the lanes of a row are summed.
+  __device__ __forceinline__ double reduce(double (&acc)[R]) const {
+    int off = LANES / 2;
+#pragma unroll
+    for (int k = R / 2; k >= 1; k >>= 1) {
+      const bool hi = (sl & off) != 0;
+#pragma unroll
+      for (int r = 0; r < k; ++r) {
+        const double give = hi ? acc[r] : acc[r + k], keep = hi ? acc[r + k] : acc[r];
+        acc[r] = keep + __shfl_xor(give, off);
+      }
+      off >>= 1;
+    }
+    double x = acc[0];
+#pragma unroll
+    for (int o = LANES / R / 2; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+    return x;
+  }
+
+  // Streams this workgroup's states of positions [kb, kb + bk) and hands every
+  // state's minimum (q, lowest action) to `commit` on lane 0 of its group;
+  // then requests the first chunks of the next positions (nbk > 0).
+  template <class F>
+  __device__ __forceinline__ void run(const uint16_t* ord, int kb, int bk, const uint16_t* nord,
+                                      int nkb, int nbk, bool prefetch, F commit) {
+    // the states of the wavefront's first lane group bound the others'
+    const int g0 = __builtin_amdgcn_readfirstlane(gid);
+    const int cnt = g0 < bk ? (bk - g0 + gstride - 1) / gstride : 0;
+    const int C = cnt * nc;
+    if (C > 0) {
+      // chunk requested last: state t (of this lane group), pass, step
+      int t = 0, pass = 0, st = 0, x = 0;
+      int s = state_at(ord, kb, bk, 0);
+      const auto next = [&]() {
+        if (++x >= C) return;  // nothing is left: the last chunk again
+        if (++st == nsteps) {
+          st = 0;
+          if (++pass * R >= m) {
+            pass = 0;
+            ++t;
+            s = state_at(ord, kb, bk, t);
+          }
+        }
+      };
+      double acc[R], qb = INFINITY;
+      int ab = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = 0.0;
+      int ct = 0, cpass = 0, cst = 0;  // chunk being used
+      const auto use = [&](const Buf& f) {
+        consume(cst, f, acc);
+        if (++cst < nsteps) return;
+        cst = 0;
+        const double sum = reduce(acc);
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = 0.0;
+        const int act = cpass * R + row_of_lane();
+        const double sc = VT == kF32 ? 1.0 : (double)f.scale;
+        const double q0 = (double)f.cost + gamma * (sc * sum);
+        double q = act < m && q0 < INFINITY ? q0 : (double)INFINITY;
+        int aq = q < INFINITY ? act : 0x7fffffff;
+#pragma unroll
+        for (int o = LANES / R; o < LANES; o <<= 1) {
+          const double q2 = __shfl_xor(q, o);
+          const int a2 = __shfl_xor(aq, o);
+          if (q2 < q || (q2 == q && a2 < aq)) {
+            q = q2;
+            aq = a2;
+          }
+        }
+        if (q < qb) {  // strictly smaller keeps the lowest action on ties
+          qb = q;
+          ab = aq;
+        }
+        if (++cpass * R < m) return;
+        cpass = 0;
+        const int i = gid + ct * gstride;
+        if (sl == 0 && i < bk) commit(i, ord ? (int)ord[kb + i] : kb + i, qb, ab);
+        ++ct;
+        qb = INFINITY;
+        ab = 0;
+      };
+      if (have) {
+        next();
+      } else {
+        load(s, pass, st, a);
+        next();
+        load(s, pass, st, b);
+      }
+      int left = C;
+      while (left > 2) {
+        use(a);
+        next();
+        load(s, pass, st, a);
+        use(b);
+        next();
+        load(s, pass, st, b);
+        left -= 2;
+      }
+      use(a);
+      if (left == 2) use(b);
+    }
+    have = false;
+    if (prefetch && g0 < nbk) {
+      int s = state_at(nord, nkb, nbk, 0);
+      load(s, 0, 0, a);
+      int pass = 0, st = 0;
+      if (nsteps > 1) {
+        st = 1;
+      } else if (R < m) {
+        pass = 1;
+      } else if (g0 + gstride < nbk) {
+        s = state_at(nord, nkb, nbk, 1);
+      }
+      load(s, pass, st, b);
+      have = true;
+    }
+  }
+
+  __device__ __forceinline__ void draw_order(uint64_t t) {
+    const OrderKey key = make_order_key(n, it->seed, t);
+    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x)
+      sh.order[t & 1][i] = (uint16_t)sweep_order_at((uint32_t)i, key);
+  }
+
+  // Arrival of this workgroup at the team's p-th meeting (p = 0, 1, ...) and
+  // the wait for the others, by thread 0 (the counter only grows).  The new
+  // values are written and read with agent-coherent accesses, so no cache is
+  // written back or invalidated.  Gives up (false, and raises the launch's
+  // abort flag) after `timeout` ticks or when another team gave up.
+  __device__ __forceinline__ bool meet(unsigned long long p) const {
+    unsigned long long* arrive = &A.ctl->arrive[it->slot];
+    const unsigned long long target = (p + 1) * (unsigned long long)K;
     __hip_atomic_fetch_add(arrive, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int ok = 1;
     const unsigned long long t0 = wall_clock64();
     while (atomic_load_agent(arrive) < target) {
-      if (__hip_atomic_load(abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-        ok = 0;
-        break;
-      }
-      if (wall_clock64() - t0 > timeout) {
-        __hip_atomic_store(abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = 0;
-        break;
+      if (__hip_atomic_load(&A.ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
+      if (wall_clock64() - t0 > A.timeout_ticks) {
+        __hip_atomic_store(&A.ctl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
       }
       __builtin_amdgcn_s_sleep(1);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    sh.ok = ok;
+    return true;
   }
-  __syncthreads();
-  return sh.ok != 0;
-}
 
-// Member `rank` of a team of I.team workgroups.  Every member runs the same
-// sequence of barriers (the stop decision is taken on the same values by
-// all), so no member waits for a barrier that another skips.
-template <int VT, int LANES>
-__device__ void batch_solve_team(const BatchItem& I, int rank, BatchShared& sh,
-                                 const BatchArgs& A) {
-  constexpr int GPW = kWave / LANES;
-  const int K = I.team;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sl = lane % LANES;
-  const int groups = (blockDim.x >> 6) * GPW;
-  const int gid = rank * groups + wave * GPW + lane / LANES;  // lane group within the team
-  const int gstride = K * groups;
-  const int64_t n = I.n, b = I.b, nb = (n + b - 1) / b;
-  unsigned long long* arrive = &A.ctl->arrive[I.slot];
-  double* dvm = A.team_dv + (size_t)I.slot * 2 * kBatchMaxTeam;  // [2][kBatchMaxTeam]
-  MBDP_GLOBAL double* gnew = gview_mut<double>(A.team_new + (size_t)I.slot * 2 * kBatchMaxB);
-  const MBDP_GLOBAL double* V0 = gview<double>(I.V);
-  for (int64_t j = threadIdx.x; j < I.ld; j += blockDim.x) sh.V[j] = j < n ? V0[j] : 0.0;
-  __syncthreads();
-  const unsigned long long t_start = wall_clock64();
-  long long sweeps = 0;
-  double dv = INFINITY;
-  int converged = 0;
-  unsigned long long phase = 0;
-  bool ok = true;
-  for (uint64_t t = 0; ok && (long long)t < A.max_sweeps; ++t) {
-    const OrderKey key = make_order_key(n, I.seed, t);
-    double dvl = 0.0;
-    for (int64_t k = 0; k < nb; ++k) {
-      const int64_t kb = k * b, bk = min(b, n - kb);
-      MBDP_GLOBAL double* buf = gnew + (phase & 1) * kBatchMaxB;
-      for (int64_t i = gid; i < bk; i += gstride) {
-        const int32_t s = (int32_t)sweep_order_at((uint32_t)(kb + i), key);
-        double q;
-        int a;
-        batch_state<VT, LANES>(I, sh.V, s, sl, q, a);
-        if (sl == 0) {
-          buf[i] = q;
+  __device__ __forceinline__ void solve(int rank) {
+    const BatchItem& I = *it;
+    const int bs = (int)I.b, nb = (n + bs - 1) / bs;
+    const bool team = K > 1;
+    double* dvm = A.team_dv + (size_t)I.slot * 2 * kBatchMaxTeam;   // [2][kBatchMaxTeam]
+    double* gnew = A.team_new + (size_t)I.slot * 2 * kBatchMaxB;    // [2][kBatchMaxB]
+    const MBDP_GLOBAL double* V0 = gview<double>(I.V);
+    for (int j = (int)threadIdx.x; j < ld; j += (int)blockDim.x) sh.V[j] = j < n ? V0[j] : 0.0;
+    draw_order(0);
+    __syncthreads();
+    const unsigned long long t_start = wall_clock64();
+    long long sweeps = 0;
+    double dv = INFINITY;
+    int converged = 0;
+    unsigned long long phase = 0;
+    bool ok = true;
+    for (uint64_t t = 0; ok && (long long)t < A.max_sweeps; ++t) {
+      const uint16_t* ord = sh.order[t & 1];
+      draw_order(t + 1);  // visible after this sweep's barriers
+      double dvl = 0.0;
+      for (int k = 0; k < nb; ++k) {
+        const int kb = k * bs, bk = min(bs, n - kb);
+        const bool last = k == nb - 1;
+        // (with one batch the next order is not yet visible to every thread)
+        const bool pre = !(last && nb == 1) && !(team && wave == 0);
+        double* buf = gnew + (phase & 1) * kBatchMaxB;
+        const auto commit = [&](int i, int s, double q, int) {
+          if (team)
+            store_shared(&buf[i], q);
+          else
+            sh.newv[i] = q;
           dvl = fmax(dvl, fabs(q - sh.V[s]));
+        };
+        run(ord, kb, bk, last ? sh.order[(t + 1) & 1] : ord, last ? 0 : kb + bs,
+            last ? min(bs, n) : min(bs, n - kb - bs), pre && !team, commit);
+        if (last) {
+          const double d = wave_max_d(dvl);
+          if (lane == 0) sh.red[wave] = d;
         }
-      }
-      if (k == nb - 1) {  // this member's max |dV| of the sweep, by sweep parity
-        dvl = wave_max_d(dvl);
-        if (lane == 0) sh.red[wave] = dvl;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-          double d = 0.0;
-          for (int w = 0; w < (int)(blockDim.x >> 6); ++w) d = fmax(d, sh.red[w]);
-          gview_mut<double>(dvm)[(t & 1) * kBatchMaxTeam + rank] = d;
+        if (team) {
+          // this wavefront's values are performed; then the workgroup's
+          __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          batch_lds_barrier();
+          if (wave == 0) {
+            if (threadIdx.x == 0) {
+              if (last) {  // this member's max |dV| of the sweep, by sweep parity
+                double d = 0.0;
+                for (int w = 0; w < nw; ++w) d = fmax(d, sh.red[w]);
+                store_shared(&dvm[(t & 1) * kBatchMaxTeam + rank], d);
+                __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+              }
+              // buffers of parity p are rewritten at phase p + 2, after meeting
+              // p + 1, which every member reaches only once it has read them
+              sh.ok = meet(phase);
+            }
+          } else if (pre) {
+            const int nbk = last ? min(bs, n) : min(bs, n - kb - bs);
+            run(nullptr, 0, 0, last ? sh.order[(t + 1) & 1] : ord, last ? 0 : kb + bs, nbk, true,
+                commit);
+          }
+          batch_lds_barrier();
+          ok = sh.ok != 0;
+          if (!ok) break;
+          for (int i = (int)threadIdx.x; i < bk; i += (int)blockDim.x)
+            sh.V[ord[kb + i]] = load_shared(&buf[i]);
+          ++phase;
+        } else {
+          batch_lds_barrier();  // every state of the batch read the values before it
+          for (int i = (int)threadIdx.x; i < bk; i += (int)blockDim.x) sh.V[ord[kb + i]] = sh.newv[i];
         }
+        batch_lds_barrier();  // committed before the next batch reads
       }
-      // buffers of parity p are rewritten at phase p + 2, after barrier p + 1,
-      // which every member reaches only once it has read them
-      ok = team_sync(arrive, &A.ctl->abort, (phase + 1) * (unsigned long long)K,
-                     A.timeout_ticks, sh);
       if (!ok) break;
-      for (int64_t i = threadIdx.x; i < bk; i += blockDim.x)
-        sh.V[sweep_order_at((uint32_t)(kb + i), key)] = buf[i];
-      ++phase;
-      __syncthreads();  // committed before the next batch reads
+      ++sweeps;
+      dv = 0.0;
+      if (team)
+        for (int r = 0; r < K; ++r) dv = fmax(dv, load_shared(&dvm[(t & 1) * kBatchMaxTeam + r]));
+      else
+        for (int w = 0; w < nw; ++w) dv = fmax(dv, sh.red[w]);
+      if (dv <= A.tol) {
+        converged = 1;
+        break;
+      }
+      batch_lds_barrier();  // sh.red and the order of sweep t - 1 are written again
     }
-    if (!ok) break;
-    ++sweeps;
-    dv = 0.0;
-    for (int r = 0; r < K; ++r) dv = fmax(dv, gview<double>(dvm)[(t & 1) * kBatchMaxTeam + r]);
-    if (dv <= A.tol) {
-      converged = 1;
-      break;
-    }
-  }
-  if (ok) {
-    if (rank == 0) {
-      MBDP_GLOBAL double* Vout = gview_mut<double>(I.V);
-      for (int64_t j = threadIdx.x; j < n; j += blockDim.x) Vout[j] = sh.V[j];
-    }
-    if (I.policy) {
-      MBDP_GLOBAL int32_t* pol = gview_mut<int32_t>(I.policy);
-      for (int64_t s = gid; s < n; s += gstride) {
-        double q;
-        int a;
-        batch_state<VT, LANES>(I, sh.V, (int32_t)s, sl, q, a);
-        if (sl == 0) pol[s] = a;
+    have = false;
+    __syncthreads();
+    if (ok) {
+      // results: V, and the greedy policy at the final V
+      if (rank == 0) {
+        MBDP_GLOBAL double* Vout = gview_mut<double>(I.V);
+        for (int j = (int)threadIdx.x; j < n; j += (int)blockDim.x) Vout[j] = sh.V[j];
+      }
+      if (I.policy) {
+        MBDP_GLOBAL int32_t* pol = gview_mut<int32_t>(I.policy);
+        run(nullptr, 0, n, nullptr, 0, 0, false,
+            [&](int, int s, double, int act) { pol[s] = act; });
       }
     }
+    if (rank == 0 && threadIdx.x == 0) {
+      BatchStat st;
+      st.sweeps = sweeps;
+      st.dv = dv;
+      st.converged = ok ? converged : 0;
+      st.pad = ok ? 0 : 1;
+      st.t_start = t_start;  // member 0's: the team starts together
+      st.t_end = wall_clock64();
+      A.stats[I.index] = st;
+    }
+    __syncthreads();
   }
-  if (rank == 0 && threadIdx.x == 0) {
-    BatchStat st;
-    st.sweeps = sweeps;
-    st.dv = dv;
-    st.converged = ok ? converged : 0;
-    st.pad = ok ? 0 : 1;
-    st.t_start = t_start;  // member 0's: the team starts together
-    st.t_end = wall_clock64();
-    A.stats[I.index] = st;
-  }
-  __syncthreads();
+};
+
+// Out of line: each value type and width has its own register allocation.
+template <int VT, int LANES>
+__device__ __noinline__ void batch_solve(const BatchItem* it, int rank, BatchArgs A) {
+  BatchSolver<VT, LANES>(it, rank, batch_shared(), A).solve(rank);
 }
 
 template <int VT>
-__device__ __forceinline__ void batch_dispatch_lanes(const BatchItem& I, int rank,
-                                                     BatchShared& sh, const BatchArgs& A) {
-  if (I.team > 1) {
-    if (I.lanes == 16)
-      batch_solve_team<VT, 16>(I, rank, sh, A);
-    else if (I.lanes == 32)
-      batch_solve_team<VT, 32>(I, rank, sh, A);
-    else
-      batch_solve_team<VT, 64>(I, rank, sh, A);
-  } else if (I.lanes == 16) {
-    batch_solve_item<VT, 16>(I, sh, A.stats, A.tol, A.max_sweeps);
-  } else if (I.lanes == 32) {
-    batch_solve_item<VT, 32>(I, sh, A.stats, A.tol, A.max_sweeps);
-  } else {
-    batch_solve_item<VT, 64>(I, sh, A.stats, A.tol, A.max_sweeps);
-  }
+__device__ __forceinline__ void batch_dispatch_lanes(const BatchItem* it, int rank,
+                                                     const BatchArgs& A) {
+  if (it->lanes == 16)
+    batch_solve<VT, 16>(it, rank, A);
+  else if (it->lanes == 32)
+    batch_solve<VT, 32>(it, rank, A);
+  else
+    batch_solve<VT, 64>(it, rank, A);
 }
 
 // Tickets 0, 1, ... are handed out in order; item i owns the tickets
 // [ticket0, ticket0 + team), the items ordered by ticket0.
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 batch_kernel(BatchArgs A) {
-  __shared__ BatchShared sh;
+  BatchShared& sh = batch_shared();
   const BatchItem& last = A.items[A.count - 1];
   const long long tickets = last.ticket0 + last.team;
   while (true) {
@@ -410,19 +516,19 @@ batch_kernel(BatchArgs A) {
     const int it = sh.item, rank = sh.rank;
     __syncthreads();
     if (it >= A.count) break;
-    const BatchItem I = A.items[it];
-    if (I.dtype == kBF16)
-      batch_dispatch_lanes<kBF16>(I, rank, sh, A);
-    else if (I.dtype == kFP8)
-      batch_dispatch_lanes<kFP8>(I, rank, sh, A);
+    const BatchItem* item = A.items + it;
+    if (item->dtype == kBF16)
+      batch_dispatch_lanes<kBF16>(item, rank, A);
+    else if (item->dtype == kFP8)
+      batch_dispatch_lanes<kFP8>(item, rank, A);
     else
-      batch_dispatch_lanes<kF32>(I, rank, sh, A);
+      batch_dispatch_lanes<kF32>(item, rank, A);
     if (__hip_atomic_load(&A.ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
   }
 }
 
 int launch_batch(const BatchArgs& a, int blocks, void* stream) {
-  hipLaunchKernelGGL(batch_kernel, dim3(blocks), dim3(1024), 0,
+  hipLaunchKernelGGL(batch_kernel, dim3(blocks), dim3(kBatchThreads), 0,
                      reinterpret_cast<hipStream_t>(stream), a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -216,6 +216,8 @@ constexpr int64_t kBatchMaxN = 8192;  // states (and row stride) per MDP
 constexpr int64_t kBatchMaxB = 4096;  // batch size per MDP
 constexpr int32_t kBatchMaxM = 64;    // actions per MDP
 constexpr int32_t kBatchMaxTeam = 16; // workgroups per MDP
+// 8 wavefronts of up to 256 registers: two chunk buffers and the FP64 sums
+constexpr int kBatchThreads = 512;
 constexpr int32_t kBatchTeamSlots = 256;  // MDPs served by a team at once
 
 struct BatchItem {

@@ -693,9 +693,7 @@ mbdp_status mdp_batch_upload(const mbdp_batch_item* items, int32_t count, void* 
     b.seed = it.seed;
     b.V = it.V;
     b.policy = it.policy;
-    // default lane group: a step of the group should cover about a row
-    const int epl = it.dtype == MBDP_F32 ? 4 : (it.dtype == MBDP_BF16 ? 8 : 16);
-    b.lanes = it.lanes ? it.lanes : (it.ld >= 64 * epl ? 64 : (it.ld >= 32 * epl ? 32 : 16));
+    b.lanes = it.lanes;  // 0: chosen with the team size
     b.index = i;
     b.team = it.team;
     b.slot = -1;
@@ -704,10 +702,17 @@ mbdp_status mdp_batch_upload(const mbdp_batch_item* items, int32_t count, void* 
     const double bytes = (double)it.n * it.m * it.ld * (it.dtype == MBDP_F32 ? 4 : it.dtype == MBDP_BF16 ? 2 : 1);
     work[(size_t)i] = bytes * (13.8 / -log(it.gamma));
   }
-  // Team sizes.  An MDP whose work exceeds the device's fair share (total
-  // work / compute units) gets that many workgroups, at most kBatchMaxTeam
-  // and at most 2 b / (lane groups per workgroup); all members of all teams
-  // must fit on the device at once (one workgroup per compute unit).
+  // Team sizes, at most kBatchMaxTeam and a lane group per state of a batch;
+  // all members of all teams must fit on the device at once (one workgroup
+  // per compute unit).
+  // Up to as many MDPs as compute units: everything starts at once, so the
+  // longest solve decides.  Workgroups are given one by one to the MDP whose
+  // estimated time is the longest, while that shortens it.  (Sizes by each
+  // MDP's share of the work left MDPs below 1.5 shares to one workgroup,
+  // behind the teams in the queue: 96 MDPs of 256 to 2048 states kept 40% of
+  // the compute units busy.)
+  // More MDPs: one whose work exceeds the device's fair share (total work /
+  // compute units) gets that many workgroups, the rest follow one by one.
   int device = 0, cus = 0;
   MBDP_HIP(hipGetDevice(&device));
   MBDP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
@@ -721,16 +726,48 @@ mbdp_status mdp_batch_upload(const mbdp_batch_item* items, int32_t count, void* 
   const int32_t slots = batch_team_slots(count);
   int64_t members = 0;
   int32_t teams = 0;
+  const auto team_cap = [&](const BatchItem& b) {
+    const int64_t groups = kBatchThreads / (b.lanes ? b.lanes : 32);  // states served at once
+    return (int32_t)std::min<int64_t>(kBatchMaxTeam, std::max<int64_t>(1, (b.b + groups - 1) / groups));
+  };
+  if (count <= cus && cus >= 2 * kBatchMaxTeam) {
+    // microseconds of a solve by t workgroups: rows at a compute unit's share
+    // of the memory rate, and per batch two workgroup barriers or a meeting
+    const auto time_of = [&](int32_t i, int32_t t) {
+      const BatchItem& b = table[(size_t)i];
+      const double sweeps = 13.8 / -log(b.gamma);
+      const double batches = (double)((b.n + b.b - 1) / b.b);
+      return work[(size_t)i] / (25e3 * t) + sweeps * batches * (t > 1 ? 6.0 : 2.0);
+    };
+    int64_t used = 0;
+    std::vector<int32_t> open;
+    for (int32_t i = 0; i < count; ++i) {
+      BatchItem& b = table[(size_t)i];
+      if (b.team == 0) {
+        b.team = 1;
+        open.push_back(i);
+      }
+      used += b.team;
+    }
+    while (used < cus && !open.empty()) {
+      int32_t best = open[0];
+      for (int32_t i : open)
+        if (time_of(i, table[(size_t)i].team) > time_of(best, table[(size_t)best].team)) best = i;
+      BatchItem& b = table[(size_t)best];
+      if (b.team >= team_cap(b)) break;
+      // (the first step to a team pays the meetings: look two workgroups ahead)
+      if (time_of(best, b.team + 2) >= time_of(best, b.team)) break;
+      ++b.team;
+      ++used;
+    }
+  }
   for (int32_t i = 0; i < count; ++i) {
     BatchItem& b = table[(size_t)i];
     if (b.team != 0 || cus < 2 * kBatchMaxTeam) continue;
-    const int64_t groups = 1024 / b.lanes;
     // a team runs below one workgroup's rate per member (team barriers), so
     // it gets half again its share, to end with the rest of the launch
     int64_t k = (int64_t)ceil(1.5 * work[(size_t)i] / share);
-    // at least half a state per lane group of each member per batch
-    const int64_t kcap = std::min<int64_t>(kBatchMaxTeam, std::max<int64_t>(1, 2 * b.b / groups));
-    b.team = (int32_t)std::max<int64_t>(1, std::min(k, kcap));
+    b.team = (int32_t)std::max<int64_t>(1, std::min<int64_t>(k, team_cap(b)));
   }
   for (int32_t i = 0; i < count; ++i) {
     BatchItem& b = table[(size_t)i];
@@ -754,6 +791,14 @@ mbdp_status mdp_batch_upload(const mbdp_batch_item* items, int32_t count, void* 
     return fail(MBDP_ERR_UNSUPPORTED,
                 "teams need %lld workgroups in %d teams; the device runs %d at once and a "
                 "launch serves %d teams", (long long)members, teams, cus, slots);
+  // Default lane group.  A lone workgroup was fastest (or within 5%) with 16
+  // lanes for every value type and row length from 128 to 3008 (BF16, 768
+  // values: 288 us per sweep, 313 with 32 lanes, 552 with 64; FP32, 3008
+  // values: 6436 / 6146 / 8882).  A team's member has few states per batch:
+  // groups of 32 lanes share them out more evenly (96 MDPs of 256 to 2048
+  // states, BF16: 189 ms against 301 ms with 16 lanes).
+  for (BatchItem& b : table)
+    if (b.lanes == 0) b.lanes = b.team > 1 ? 32 : 16;
   // queue order: the teams first (all their members start at once), then the
   // single workgroups, each part heaviest per workgroup first
   std::vector<int32_t> order((size_t)count);
