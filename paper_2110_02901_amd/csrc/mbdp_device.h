@@ -295,4 +295,27 @@ __device__ __forceinline__ bool grid_sync(GridBarrier& g, bool release = true,
   return s_abort == 0;
 }
 
+// The same for workgroups that share data with their neighbours lo .. hi only
+// (this one among them): waits until each of those has passed as many
+// barriers, without a release word.  Everything shared was stored through
+// (agent-coherent) and is read that way, as with grid_sync(g, false, false).
+// A neighbour can be one barrier ahead at most, and the others further: the
+// differences between workgroups average out over the barriers instead of
+// adding up the slowest of each.
+__device__ __forceinline__ bool neighbour_sync(GridBarrier& g, int lo, int hi) {
+  __shared__ int s_bad;
+  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
+  g.gen += 1;
+  unsigned long long* slots = g.ctl->bar_slots;
+  if (threadIdx.x == 0) atomic_store_agent(&slots[blockIdx.x], g.gen);
+  bool ok = true;
+  for (int i = lo + (int)threadIdx.x; i <= hi && ok; i += (int)blockDim.x)
+    ok = wait_at_least(&slots[i], g.gen, g);
+  if (!ok) s_bad = 1;
+  __syncthreads();
+  return s_bad == 0;
+}
+
 }  // namespace mbdp
