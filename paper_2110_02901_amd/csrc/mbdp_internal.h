@@ -136,7 +136,9 @@ struct WsLayout {
   size_t zero_bytes;  // prefix cleared before every launch (control + counters)
   // The resident-value kernel's exchange words uint64[2][n] lie over the first-batch
   // stamps and the sweep orders, which it does not use; its cleared prefix ends with them.
-  size_t xch, zero_bytes_resident;
+  // The FP64 correction's words are twice as many and reach over the split
+  // partials, the V partner (its policy is in LDS) and into the shifted costs.
+  size_t xch, zero_bytes_resident, zero_bytes_resident64;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -155,6 +157,7 @@ inline WsLayout ws_layout(int32_t storage, int64_t n, int32_t m, int64_t max_uni
   w.order = off;      off = align_up(off + 3 * (size_t)n * sizeof(int32_t), 256);
   w.xch = w.first_mark;
   w.zero_bytes_resident = w.xch + 2 * (size_t)n * sizeof(uint64_t);
+  w.zero_bytes_resident64 = w.xch + 4 * (size_t)n * sizeof(uint64_t);
   w.partial = off;
   if (storage == kDense) off = align_up(off + (size_t)max_units * (size_t)m * sizeof(float), 256);
   w.vbuf1 = off;      off = align_up(off + (size_t)n * sizeof(float), 256);
@@ -192,7 +195,8 @@ int launch_solve(KParams p, const WsLayout& w, LaunchShape shape, void* stream, 
                  size_t errlen);
 // The FP64 correction kernel (mbdp_refine.hip) for an FP32 handle; the same
 // contract as launch_solve.
-int launch_refine(KParams p, LaunchShape shape, void* stream, char* err, size_t errlen);
+int launch_refine(KParams p, const WsLayout& w, LaunchShape shape, void* stream, char* err,
+                  size_t errlen);
 // The kernel family launch_solve would run for p (no device work).
 int query_engine(const KParams& p, LaunchShape shape, int* engine, char* err, size_t errlen);
 int launch_zero(void* ptr, size_t bytes, void* stream);
@@ -377,6 +381,9 @@ SolveFn pick_band_lp(const KParams& p, int units_per_wave_hint);
 // a row of a cached table, 8 steps of a streamed row (a step is 1 KB).
 enum ResShape : int { kResShort, kResCached, kResStream };
 SolveFn pick_resident(const KParams& p, ResShape shape);
+bool resident_plan(KParams& p, LaunchShape& shape, SolveFn* fn, int* blocks);
+int launch_resident(KParams p, const WsLayout& w, SolveFn f, int blocks, LaunchShape shape,
+                    void* stream, char* err, size_t errlen);
 SolveFn pick_resident_lp(const KParams& p, ResShape shape);
 
 }  // namespace mbdp

@@ -441,8 +441,9 @@ static int grid_blocks(SolveFn f, const LaunchShape& shape, int* blocks, char* e
 // LDS, as do the states of a workgroup's units of a sweep, and the batch's
 // words fit the exchange.  Fills the parts per position and the grid; false
 // where the general dense engine runs.
-static bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blocks) {
-  if (p.storage != kDense || p.n > kResMaxStates) return false;
+bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blocks) {
+  if (p.storage != kDense || p.n > (p.task == kTaskRefine ? kResMaxStates / 2 : kResMaxStates))
+    return false;
   LaunchShape shape = shape0;
   if (shape.threads > kResThreads) shape.threads = kResThreads;
   const int64_t wb = p.vdtype == kF32 ? 4 : (p.vdtype == kBF16 ? 2 : 1);
@@ -461,7 +462,8 @@ static bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blo
   if (!f || grid_blocks(f, shape, &g, err, sizeof err) != 0) return false;
   if (g > shape.cus) g = shape.cus;  // one per CU: the LDS holds one
   if (g > p.n) g = (int)p.n;
-  const bool policy = p.task == kTaskMPI || (p.task == kTaskSweep && p.policy_sweep);
+  const bool policy = p.task == kTaskMPI || (p.task == kTaskSweep && p.policy_sweep) ||
+                      (p.task == kTaskRefine && p.K > 0);
   // one workgroup where a batch is so short that the exchange between
   // workgroups would cost more than its rows
   const int64_t batch_bytes = p.b * p.m * p.n * wb;
@@ -554,12 +556,9 @@ int query_engine(const KParams& q, LaunchShape shape, int* engine, char* err, si
   return choose(p, shape, &f, &blocks, engine, err, errlen);
 }
 
-int launch_solve(KParams p, const WsLayout& w, LaunchShape shape, void* stream, char* err,
-                 size_t errlen) {
-  SolveFn f = nullptr;
-  int blocks = 0, engine = 0;
-  if (choose(p, shape, &f, &blocks, &engine, err, errlen) != 0) return -1;
-  if (engine == kEngineResident && blocks == 1) {
+int launch_resident(KParams p, const WsLayout& w, SolveFn f, int blocks, LaunchShape shape,
+                    void* stream, char* err, size_t errlen) {
+  if (blocks == 1) {
     // no other workgroup to be co-resident with, and the kernel clears its own status words
     hipLaunchKernelGGL(f, dim3(1), dim3(shape.threads), 0, reinterpret_cast<hipStream_t>(stream), p);
     const hipError_t e = hipGetLastError();
@@ -567,7 +566,30 @@ int launch_solve(KParams p, const WsLayout& w, LaunchShape shape, void* stream, 
     snprintf(err, errlen, "launch failed: %s", hipGetErrorString(e));
     return -1;
   }
-  if (launch_zero(p.ctl, engine == kEngineResident ? w.zero_bytes_resident : w.zero_bytes, stream) != 0) {
+  const size_t clear = p.task == kTaskRefine ? w.zero_bytes_resident64 : w.zero_bytes_resident;
+  if (launch_zero(p.ctl, clear, stream) != 0) {
+    snprintf(err, errlen, "workspace clear failed: %s", hipGetErrorString(hipGetLastError()));
+    return -1;
+  }
+  void* args[] = {&p};
+  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(f), dim3(blocks),
+                                                  dim3(shape.threads), args, 0,
+                                                  reinterpret_cast<hipStream_t>(stream));
+  if (e != hipSuccess) {
+    snprintf(err, errlen, "cooperative launch (%d x %d) failed: %s", blocks, shape.threads,
+             hipGetErrorString(e));
+    return -1;
+  }
+  return 0;
+}
+
+int launch_solve(KParams p, const WsLayout& w, LaunchShape shape, void* stream, char* err,
+                 size_t errlen) {
+  SolveFn f = nullptr;
+  int blocks = 0, engine = 0;
+  if (choose(p, shape, &f, &blocks, &engine, err, errlen) != 0) return -1;
+  if (engine == kEngineResident) return launch_resident(p, w, f, blocks, shape, stream, err, errlen);
+  if (launch_zero(p.ctl, w.zero_bytes, stream) != 0) {
     snprintf(err, errlen, "workspace clear failed: %s", hipGetErrorString(hipGetLastError()));
     return -1;
   }

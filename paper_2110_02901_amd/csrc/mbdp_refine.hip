@@ -18,10 +18,16 @@
 // One persistent cooperative launch runs the whole correction with the
 // solvers' driver (orders, batches, ping-pong buffers, grid barriers) over
 // FP64 buffers.  The engines:
-//  * dense: a workgroup per state streams the state's m rows (8 rows at a
-//    time, two 16-byte loads per row and thread, V reused from registers
-//    across the rows) against V staged in LDS (n <= 8192) or read from
-//    memory; in policy sweeps a wavefront per state;
+//  * dense, n <= 8192: the resident-value kernel (mbdp_resident.h) with an
+//    FP64 V in LDS, two tagged words per value in the exchange.  Against the
+//    engine below with V staged in LDS per batch (a workgroup per state, two
+//    workgroup barriers per 8 rows, a grid barrier per batch) 4096 x 8,
+//    b = 512, went from 19.2 to 9.6 ms a correction (5.0 ms of rows at
+//    6.5 TB/s);
+//  * dense, larger (V does not fit in LDS) or with rows shorter than a load:
+//    a workgroup per state streams the state's m rows (8 rows at a time, one
+//    16-byte load per row and thread, V reused from registers across the
+//    rows) against V in memory; in policy sweeps a wavefront per state;
 //  * constant row length k: a wavefront per state, k/4 lanes per row, V
 //    gathered in FP64; in policy sweeps a lane group per state;
 //  * general CSR: a wavefront per state, lanes striding each row.
@@ -77,13 +83,10 @@ __device__ __forceinline__ void lds_argmin(const double* s_q, int m, double& qv,
   if (av == 0x7fffffff) av = 0;
 }
 
-constexpr int kStage64 = 8192;  // FP64 values of V staged in LDS (64 KB)
-
 // LDS of the dense engine, one instance per kernel whatever the template
 // instantiations that use it (a __shared__ variable inside a template
 // exists once per instantiation).
 struct Dense64Shared {
-  double v[kStage64];        // V staged for the batch
   double q[kMaxActions];     // Q of the state's actions
   double red[16][8];         // per-wavefront row sums
 };
@@ -107,7 +110,6 @@ struct Dense64Engine {
   static constexpr int U = 1;   // column steps in flight (R * U 16-byte loads per thread)
 
   // acc[r] += row r . V over this thread's columns (all n), rows r < nrows.
-  template <bool STAGED>
   __device__ __forceinline__ static void dot_rows(const float* __restrict__ rows, uint32_t n,
                                                   int nrows, const double* __restrict__ V,
                                                   double (&acc)[R]) {
@@ -160,7 +162,7 @@ struct Dense64Engine {
     }
   }
 
-  template <bool STAGED, bool IDENT, class Acc>
+  template <bool IDENT, class Acc>
   __device__ __forceinline__ static void batch_min(const KParams& p, const int32_t* ord,
                                                    int64_t bk, const CtxT<double>& c,
                                                    const double* V, int mode, Acc& L) {
@@ -182,7 +184,7 @@ struct Dense64Engine {
         double acc[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r] = 0.0;
-        dot_rows<STAGED>(p.P + ((size_t)s * m + a0) * n, n, nrows, V, acc);
+        dot_rows(p.P + ((size_t)s * m + a0) * n, n, nrows, V, acc);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const double x = wave_sum_d(acc[r]);
@@ -214,7 +216,7 @@ struct Dense64Engine {
   }
 
   // Policy sweeps: a wavefront per state, the state's one row.
-  template <bool STAGED, class Acc>
+  template <class Acc>
   __device__ __forceinline__ static void batch_policy(const KParams& p, const int32_t* ord,
                                                       int64_t bk, const CtxT<double>& c,
                                                       const double* V, Acc& L) {
@@ -276,23 +278,12 @@ struct Dense64Engine {
   template <bool CE, bool IDENT, class Acc>
   __device__ __forceinline__ static void batch(const KParams& p, const int32_t* ord, int64_t bk,
                                                const CtxT<double>& c, int mode, Acc& L) {
-    double* s_v = dense64_shared().v;
     const int64_t units_per_wg = mode == kModePolicy ? (int64_t)(blockDim.x >> 6) : 1;
     if ((int64_t)blockIdx.x * units_per_wg >= bk) return;  // uniform over the workgroup
-    if (p.n <= kStage64) {
-      for (int64_t j = threadIdx.x; j < p.n; j += blockDim.x) s_v[j] = c.rd[j];
-      __syncthreads();
-      if (mode == kModePolicy)
-        batch_policy<true>(p, ord, bk, c, s_v, L);
-      else
-        batch_min<true, IDENT>(p, ord, bk, c, s_v, mode, L);
-      __syncthreads();  // s_v is rewritten by the next batch
-    } else {
-      if (mode == kModePolicy)
-        batch_policy<false>(p, ord, bk, c, c.rd, L);
-      else
-        batch_min<false, IDENT>(p, ord, bk, c, c.rd, mode, L);
-    }
+    if (mode == kModePolicy)
+      batch_policy(p, ord, bk, c, c.rd, L);
+    else
+      batch_min<IDENT>(p, ord, bk, c, c.rd, mode, L);
   }
 };
 
@@ -553,7 +544,20 @@ static SolveFn pick_refine(const KParams& p) {
   return &refine_kernel<Csr64Engine>;
 }
 
-int launch_refine(KParams p, LaunchShape shape, void* stream, char* err, size_t errlen) {
+int launch_refine(KParams p, const WsLayout& w, LaunchShape shape, void* stream, char* err,
+                  size_t errlen) {
+  KParams q = p;
+  LaunchShape qshape = shape;
+  SolveFn resident = nullptr;
+  int grid = 0;
+  if (p.vdtype == kF32 && resident_plan(q, qshape, &resident, &grid)) {
+    if (!q.want_policy_out) q.policy = nullptr;  // kept in LDS
+    return launch_resident(q, w, resident, grid, qshape, stream, err, errlen);
+  }
+  if (launch_zero(p.ctl, w.zero_bytes, stream) != 0) {
+    snprintf(err, errlen, "workspace clear failed: %s", hipGetErrorString(hipGetLastError()));
+    return -1;
+  }
   SolveFn f = pick_refine(p);
   if (!f) {
     snprintf(err, errlen, "the FP64 correction needs FP32 transition values");

@@ -26,7 +26,8 @@
 // barrier per batch: 8192 x 16, b = 1024 in FP32 96.3 -> 85.3 us (5.6 -> 6.3 TB/s
 // of rows), in FP8 44.9 -> 25.6 us (3.0 -> 5.2 TB/s); 500 x 6, b = 100 26.4 ->
 // 5.9 us.  Modified policy iteration of 6166 x 4 (b = 512, rows of 4-byte
-// alignment) 104 -> 38.6 ms; one sweep of 64 x 4 108 -> 26.7 us a call.
+// alignment) 104 -> 38.6 ms; one sweep of 64 x 4 108 -> 26.7 us a call; the
+// FP64 correction of 4096 x 8 (b = 512) 19.2 -> 9.6 ms.
 
 #pragma once
 
@@ -49,6 +50,22 @@ __device__ __forceinline__ void lds_barrier() {
 // 16 lanes, then across the four rows; every lane gets the result.
 #define MBDP_DPP_ADD(v, ctrl) \
   ((v) + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), (ctrl), 0xF, 0xF, true)))
+#define MBDP_DPP_ADD_D(v, ctrl)                                                              \
+  ((v) + __hiloint2double(                                                                   \
+             __builtin_amdgcn_mov_dpp(__double2hiint(v), (ctrl), 0xF, 0xF, true),            \
+             __builtin_amdgcn_mov_dpp(__double2loint(v), (ctrl), 0xF, 0xF, true)))
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  v = MBDP_DPP_ADD_D(v, 0xB1);
+  v = MBDP_DPP_ADD_D(v, 0x4E);
+  v = MBDP_DPP_ADD_D(v, 0x141);
+  v = MBDP_DPP_ADD_D(v, 0x140);
+  const int h = __double2hiint(v), l = __double2loint(v);
+  double r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    r[i] = __hiloint2double(__builtin_amdgcn_readlane(h, 16 * i), __builtin_amdgcn_readlane(l, 16 * i));
+  return (r[0] + r[1]) + (r[2] + r[3]);
+}
 __device__ __forceinline__ float wave_sum_dpp(float v) {
   v = MBDP_DPP_ADD(v, 0xB1);   // quad_perm [1,0,3,2]
   v = MBDP_DPP_ADD(v, 0x4E);   // quad_perm [2,3,0,1]
@@ -77,14 +94,18 @@ struct alignas(16) ResBatch {
   int pad[2];
 };
 
+// VT: float for the solvers (W = V - R), double for the FP64 correction (V
+// itself, up to half as many states).
+template <class VT>
 struct ResShared {
-  float V[kResMaxStates];              // W of every state (layout ResRows::at), zero beyond n
+  static constexpr int kStates = kResMaxStates * 4 / (int)sizeof(VT);
+  VT V[kStates];                       // W of every state (layout ResRows::at), zero beyond n
   uint16_t pol[kResMaxStates];         // the policy (policy sweeps, MPI)
   uint16_t list[2][kResList];          // states of this workgroup's units, by sweep parity
   double q[kResQ];                     // Q of the rows of a round (their cost while segments are open)
   double seg[64];                      // segment sums of rows split over wavefronts
   unsigned cnt[kResQ];                 // finished tasks per unit of the round
-  unsigned long long x[kResSolo];      // the batch's words of a lone workgroup
+  unsigned long long x[sizeof(VT) / 4 * kResSolo];  // the batch's words of a lone workgroup
   unsigned long long resid;            // max |TW - W| of an improvement pass (FP64 bits)
   double s_dv[4], s_err[4], s_resid;   // sweep statistics by communicating wavefront
   unsigned s_wabs[4];
@@ -93,9 +114,24 @@ struct ResShared {
   ResBatch desc[3];                    // a full batch, the sweep's last, an improvement pass
 };
 
-__device__ __forceinline__ ResShared& res_shared() {
-  __shared__ ResShared sh;
+template <class VT>
+__device__ __forceinline__ ResShared<VT>& res_shared() {
+  __shared__ ResShared<VT> sh;
   return sh;
+}
+
+template <int TASK>
+struct ResValue {
+  typedef float type;
+};
+template <>
+struct ResValue<kTaskRefine> {
+  typedef double type;
+};
+
+// Whether the sweeps of a call apply a policy (else the minimum).
+__host__ __device__ __forceinline__ bool res_policy_sweeps(int task, int policy_sweep, int K) {
+  return task == kTaskMPI || (task == kTaskSweep && policy_sweep) || (task == kTaskRefine && K > 0);
 }
 
 // A row of P as 16-byte loads.  One step of a wavefront covers kStep
@@ -137,9 +173,15 @@ __device__ __forceinline__ u4 res_load(const uint8_t* p0) {
 // A chunk of a wavefront is RC rows of U steps: RC = 1 for long rows (the
 // whole wavefront streams one row at a time), several rows side by side
 // where a row is only a step or two, so that one chunk's latency serves them.
-template <class T, bool NT, bool TAIL, int RC, int U>
+template <class T, bool NT, bool TAIL, int RC, int U, class VT>
 struct ResEngine {
   using Rows = ResRows<T>;
+  using Shared = ResShared<VT>;
+  static constexpr bool k64 = sizeof(VT) == 8;
+  // 64-bit words of a value: (tag, state, FP32 value), or the two halves of
+  // an FP64 value, each with the tag
+  static constexpr int kWords = k64 ? 2 : 1;
+  typedef VT v4 __attribute__((ext_vector_type(4)));
 
   struct Buf {
     u4 x[RC * U];
@@ -149,7 +191,7 @@ struct ResEngine {
   };
 
   const MBDP_CONST KParams* p;
-  ResShared& sh;
+  Shared& sh;
   int g, G, lane, wave, nw, lgnw, ncw;  // lgnw: log2 of the wavefronts
   int n, m, bs, nsteps;   // bs: the batch size
   bool shifted;           // costs are c' (after the first re-centring)
@@ -168,7 +210,7 @@ struct ResEngine {
 
   __device__ __forceinline__ void refresh() { __asm__ volatile("" : "+s"(p)); }
 
-  __device__ __forceinline__ ResEngine(const MBDP_CONST KParams* kp, ResShared& s) : p(kp), sh(s) {
+  __device__ __forceinline__ ResEngine(const MBDP_CONST KParams* kp, Shared& s) : p(kp), sh(s) {
     g = (int)blockIdx.x;
     G = (int)gridDim.x;
     lane = threadIdx.x & 63;
@@ -345,12 +387,17 @@ struct ResEngine {
     if constexpr (T::kType != kF32) f.scale = rscale[t.at];
   }
 
-  // FP32 sums of a task: four per row where one row is streamed (their order
+  // Sums of a task: four per row where one row is streamed (their order
   // is that of the columns of a lane mod 4), one per row otherwise.
   static constexpr int kAcc = RC == 1 ? 4 : RC;
 
-  __device__ __forceinline__ static void step(const u4& x, const f4* v, float (&acc)[kAcc], int r) {
-    if constexpr (T::kType == kF32) {
+  __device__ __forceinline__ static void step(const u4& x, const v4* v, VT (&acc)[kAcc], int r) {
+    if constexpr (k64) {  // FP32 rows
+      acc[RC == 1 ? 0 : r] = fma((double)__uint_as_float(x.x), v[0].x, acc[RC == 1 ? 0 : r]);
+      acc[RC == 1 ? 1 : r] = fma((double)__uint_as_float(x.y), v[0].y, acc[RC == 1 ? 1 : r]);
+      acc[RC == 1 ? 2 : r] = fma((double)__uint_as_float(x.z), v[0].z, acc[RC == 1 ? 2 : r]);
+      acc[RC == 1 ? 3 : r] = fma((double)__uint_as_float(x.w), v[0].w, acc[RC == 1 ? 3 : r]);
+    } else if constexpr (T::kType == kF32) {
       acc[RC == 1 ? 0 : r] = fmaf(__uint_as_float(x.x), v[0].x, acc[RC == 1 ? 0 : r]);
       acc[RC == 1 ? 1 : r] = fmaf(__uint_as_float(x.y), v[0].y, acc[RC == 1 ? 1 : r]);
       acc[RC == 1 ? 2 : r] = fmaf(__uint_as_float(x.z), v[0].z, acc[RC == 1 ? 2 : r]);
@@ -363,16 +410,16 @@ struct ResEngine {
 
   // acc += chunk c of the task's segment times V
   __device__ __forceinline__ void consume(const ResBatch& b, const Task& t, int c, const Buf& f,
-                                          float (&acc)[kAcc]) const {
+                                          VT (&acc)[kAcc]) const {
     const int st0 = t.seg * b.sps + c * U;
     if (U >= 4 && whole(b, t.seg, c)) {
-      const float* vb = sh.V + st0 * Rows::kStep + lane * 4;
+      const VT* vb = sh.V + st0 * Rows::kStep + lane * 4;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        f4 v[Rows::kQuads];
+        v4 v[Rows::kQuads];
 #pragma unroll
         for (int q = 0; q < Rows::kQuads; ++q)
-          v[q] = *reinterpret_cast<const f4*>(vb + u * Rows::kStep + q * 256);
+          v[q] = *reinterpret_cast<const v4*>(vb + u * Rows::kStep + q * 256);
 #pragma unroll
         for (int r = 0; r < RC; ++r) step(f.x[r * U + u], v, acc, r);
         if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four steps' V at a time in registers
@@ -383,10 +430,10 @@ struct ResEngine {
       for (int u = 0; u < U; ++u) {
         const int st = min(st0 + u, nsteps - 1);
         const bool ok = st0 + u < st1 && st * 1024 + lane * 16 <= n * T::kBytes - 16;
-        f4 v[Rows::kQuads];
+        v4 v[Rows::kQuads];
 #pragma unroll
         for (int q = 0; q < Rows::kQuads; ++q)
-          v[q] = *reinterpret_cast<const f4*>(sh.V + st * Rows::kStep + lane * 4 + q * 256);
+          v[q] = *reinterpret_cast<const v4*>(sh.V + st * Rows::kStep + lane * 4 + q * 256);
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
           const u4 x = ok ? f.x[r * U + u] : u4{0u, 0u, 0u, 0u};
@@ -399,10 +446,10 @@ struct ResEngine {
       const int s0 = t.seg * b.sps;  // (a segment past the row's end has none of it)
       if (c == b.nc - 1 && s0 < nsteps && s0 + b.sps >= nsteps) {
         const int jt = (n & ~3) + lane;
-        const float v = jt < n ? sh.V[jt] : 0.f;
+        const VT v = jt < n ? sh.V[jt] : (VT)0;
 #pragma unroll
         for (int r = 0; r < RC; ++r)
-          acc[RC == 1 ? 0 : r] = fmaf(jt < n ? f.tail[r] : 0.f, v, acc[RC == 1 ? 0 : r]);
+          acc[RC == 1 ? 0 : r] = fma(jt < n ? (VT)f.tail[r] : (VT)0, v, acc[RC == 1 ? 0 : r]);
       }
     }
   }
@@ -410,15 +457,15 @@ struct ResEngine {
   // The segment's sums are complete: their share of Q goes to LDS, and the
   // wavefront that completes a unit finds the unit's minimum and publishes it.
   __device__ __forceinline__ void finish_task(const ResBatch& b, int u0, const Task& t,
-                                              const Buf& f, const float (&acc)[kAcc]) {
-    float sum;
+                                              const Buf& f, const VT (&acc)[kAcc]) {
+    VT sum;
     if constexpr (RC == 1) {
       sum = wave_sum_dpp((acc[0] + acc[1]) + (acc[2] + acc[3]));
     } else {
-      sum = 0.f;
+      sum = (VT)0;
 #pragma unroll
       for (int r = 0; r < RC; ++r) {
-        const float x = wave_sum_dpp(acc[r]);
+        const VT x = wave_sum_dpp(acc[r]);
         sum = lane == r ? x : sum;
       }
     }
@@ -484,7 +531,7 @@ struct ResEngine {
   // The unit's result to the workgroups (and to the caller's arrays), by one lane.
   __device__ __forceinline__ void publish(const ResBatch& b, int i, int s, double q, int a) {
     const int u = g + i * G;
-    unsigned long long w;
+    unsigned long long w, w2 = 0;
     if (b.mode >= kModeImprove) {
       const double old = (double)sh.V[Rows::at(s)];
       const double d = fabs(q - old);
@@ -493,13 +540,28 @@ struct ResEngine {
       w = ((unsigned long long)(phase & 0x7FFFFFFFu) << 32) | (unsigned)a;
     } else {
       if (p->argmin_out && b.lgp == 0) p->argmin_out[s] = a;
-      w = ((unsigned long long)(0x80000000u | ((phase & 0x7FFu) << 20) | (unsigned)s) << 32) |
-          __float_as_uint((float)q);
+      const unsigned long long head =
+          (unsigned long long)(0x80000000u | ((phase & 0x7FFu) << 20) | (unsigned)s) << 32;
+      if constexpr (k64) {
+        w = head | (unsigned)__double2loint(q);
+        w2 = head | (unsigned)__double2hiint(q);
+      } else {
+        w = head | __float_as_uint((float)q);
+      }
     }
-    if (G == 1)
+    if (G == 1) {
       sh.x[u] = w;
-    else
-      atomic_store_agent(&xch[(size_t)(phase & 1) * n + u], w);
+      if (k64) sh.x[kResSolo + u] = w2;
+    } else {
+      unsigned long long* to = words_of(phase);
+      atomic_store_agent(&to[u], w);
+      if (k64 && b.mode < kModeImprove) atomic_store_agent(&to[n + u], w2);
+    }
+  }
+
+  // The phase's words: [kWords][n], by phase parity.
+  __device__ __forceinline__ unsigned long long* words_of(unsigned ph) const {
+    return xch + (size_t)(ph & 1) * kWords * n;
   }
 
   // Streams this workgroup's units of the batch, then requests the first two
@@ -513,7 +575,7 @@ struct ResEngine {
       const int C = chunks_of(b, all);
       const bool loaded = have && u0 == 0;
       if (C > 0) {
-        float acc[kAcc];
+        VT acc[kAcc];
 #pragma unroll
         for (int i = 0; i < kAcc; ++i) acc[i] = 0.f;
         // (the tasks of requested chunks were found with them)
@@ -591,9 +653,12 @@ struct ResEngine {
     // a word is at most two phases old.
     if (G > 1 && b.mode < kModeImprove && wave == nw - 1) {
       const int all = sweep_words(b.lgp);
-      for (int u = g + b.cnt * G + lane * G; u < all; u += kWave * G)
-        atomic_store_agent(&xch[(size_t)(phase & 1) * n + u],
-                           (unsigned long long)(0x80000000u | ((phase & 0x7FFu) << 20)) << 32);
+      const unsigned long long w =
+          (unsigned long long)(0x80000000u | ((phase & 0x7FFu) << 20)) << 32;
+      for (int u = g + b.cnt * G + lane * G; u < all; u += kWave * G) {
+        atomic_store_agent(&words_of(phase)[u], w);
+        if (k64) atomic_store_agent(&words_of(phase)[n + u], w);
+      }
     }
   }
 
@@ -602,21 +667,21 @@ struct ResEngine {
 
   // ---- exchange
 
-  // Words idx = base + j * stride, j < J, of the phase; false on abort.
+  // Words base + j * stride, j < J, of plane h of the phase; false on abort.
   template <int J>
   __device__ __forceinline__ bool fetch(const ResBatch& b, int base, int stride, int limit,
-                                        unsigned long long (&w)[J]) {
+                                        unsigned long long (&w)[J], int h = 0) {
     const bool imp = b.mode >= kModeImprove;
     const unsigned want = imp ? (phase & 0x7FFFFFFFu) : (0x800u | (phase & 0x7FFu));
     if (G == 1) {
 #pragma unroll
       for (int j = 0; j < J; ++j) {
         const int i = base + j * stride;
-        w[j] = sh.x[i < limit ? i : 0];
+        w[j] = sh.x[h * kResSolo + (i < limit ? i : 0)];
       }
       return true;
     }
-    const unsigned long long* src = xch + (size_t)(phase & 1) * n;
+    const unsigned long long* src = words_of(phase) + (size_t)h * n;
     unsigned long long t0 = 0;
     for (int spin = 0;; ++spin) {
       bool ok = true;
@@ -654,13 +719,17 @@ struct ResEngine {
   template <int J>
   __device__ __forceinline__ bool take(const ResBatch& b, int i0, int stride, int used, int words,
                                        unsigned& changes) {
-    unsigned long long w[J];
+    unsigned long long w[J], w2[J];
     if (!fetch<J>(b, i0 + lane, stride, words, w)) return false;
+    if constexpr (k64) {
+      if (b.mode < kModeImprove && !fetch<J>(b, i0 + lane, stride, words, w2, 1)) return false;
+    }
     if (b.mode >= kModeImprove) {
 #pragma unroll
       for (int j = 0; j < J; ++j) {
         const int i = i0 + j * stride + lane;
         if (i < used) {
+          if (k64 && p->vref) err = fmax(err, fabs((double)sh.V[i] - p->vref[i]));
           const uint16_t a = (uint16_t)(unsigned)w[j];
           changes += sh.pol[i] != a;
           sh.pol[i] = a;
@@ -673,12 +742,19 @@ struct ResEngine {
       for (int off = 1; off <= part; off <<= 1)
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-          const float v = __uint_as_float((unsigned)w[j]);
-          const float o = __shfl_xor(v, off);
-          w[j] = (w[j] & 0xFFFFFFFF00000000ull) | __float_as_uint(fminf(v, o));
+          if constexpr (k64) {
+            const double v = __hiloint2double((int)w2[j], (int)w[j]);
+            const double q = fmin(v, __shfl_xor(v, off));
+            w[j] = (w[j] & 0xFFFFFFFF00000000ull) | (unsigned)__double2loint(q);
+            w2[j] = (unsigned)__double2hiint(q);
+          } else {
+            const float v = __uint_as_float((unsigned)w[j]);
+            const float o = __shfl_xor(v, off);
+            w[j] = (w[j] & 0xFFFFFFFF00000000ull) | __float_as_uint(fminf(v, o));
+          }
         }
     }
-    float old[J];
+    VT old[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {  // (an unused word's state is read too, and dropped)
       const int s = (int)((unsigned)(w[j] >> 32) & 0xFFFFFu);
@@ -689,11 +765,15 @@ struct ResEngine {
       const int i = i0 + j * stride + lane;
       if (i < used && (i & part) == 0) {
         const int s = (int)((unsigned)(w[j] >> 32) & 0xFFFFFu);
-        const float v = __uint_as_float((unsigned)w[j]);
+        VT v;
+        if constexpr (k64)
+          v = __hiloint2double((int)w2[j], (int)w[j]);
+        else
+          v = __uint_as_float((unsigned)w[j]);
         sh.V[Rows::at(s)] = v;
         dv = fmax(dv, fabs((double)v - (double)old[j]));
         if (p->vref) err = fmax(err, fabs((double)v - (shifted ? p->tgt[s] : p->vref[s])));
-        wabs = max(wabs, __float_as_uint(v) & 0x7FFFFFFFu);
+        if constexpr (!k64) wabs = max(wabs, __float_as_uint(v) & 0x7FFFFFFFu);
       }
     }
     return true;
@@ -802,7 +882,7 @@ struct ResEngine {
     return (int)((n + p->b - 1) / p->b) * per;
   }
   __device__ __forceinline__ int list_lgp() const {
-    return p->task == kTaskMPI || (p->task == kTaskSweep && p->policy_sweep) ? 0 : p->res_lgp;
+    return res_policy_sweeps(p->task, p->policy_sweep, p->K) ? 0 : p->res_lgp;
   }
   __device__ __forceinline__ int ord_position(int e) const {  // -1: no such unit
     const int lgp = list_lgp();
@@ -973,11 +1053,13 @@ struct ResEngine {
   }
 };
 
+// Task of the kernel: a solver's, or the FP64 correction.
 template <class T, bool NT, bool TAIL, int RC, int U, int TASK>
 __global__ void __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 resident_kernel(KParams kp) {
-  ResShared& sh = res_shared();
-  using Eng = ResEngine<T, NT, TAIL, RC, U>;
+  using VT = typename ResValue<TASK>::type;
+  ResShared<VT>& sh = res_shared<VT>();
+  using Eng = ResEngine<T, NT, TAIL, RC, U, VT>;
   using Rows = typename Eng::Rows;
   Eng e((const MBDP_CONST KParams*)__builtin_amdgcn_kernarg_segment_ptr(), sh);
   const MBDP_CONST KParams*& p = e.p;
@@ -996,11 +1078,16 @@ resident_kernel(KParams kp) {
     sh.resid = 0ull;
     sh.abort = 0;
   }
-  for (int j = tid; j < e.nsteps * Rows::kStep; j += nt) sh.V[Rows::at(j)] = j < n ? p->vbuf0[j] : 0.f;
+  for (int j = tid; j < e.nsteps * Rows::kStep; j += nt) {
+    if constexpr (TASK == kTaskRefine)
+      sh.V[Rows::at(j)] = j < n ? p->vd0[j] : 0.0;
+    else
+      sh.V[Rows::at(j)] = j < n ? p->vbuf0[j] : 0.f;
+  }
   const bool policy_mode = TASK == kTaskMPI ? p->policy_is_init != 0
                                             : (TASK == kTaskSweep && p->policy_sweep);
   if (gridDim.x == 1) __syncthreads();  // the status words are clear before an error is raised
-  if (policy_mode || TASK == kTaskMPI)
+  if (policy_mode || TASK == kTaskMPI || TASK == kTaskRefine)
     for (int s = tid; s < n; s += nt) {
       int a = policy_mode ? p->policy[s] : 0;
       if (a < 0 || a >= p->m) {
@@ -1009,7 +1096,7 @@ resident_kernel(KParams kp) {
       }
       sh.pol[s] = (uint16_t)a;
     }
-  const int smode = TASK == kTaskMPI || (TASK == kTaskSweep && p->policy_sweep) ? kModePolicy : kModeMin;
+  const int smode = res_policy_sweeps(TASK, p->policy_sweep, p->K) ? kModePolicy : kModeMin;
   if (tid < 3) e.describe(tid, smode);
   const int nb = (int)((n + p->b - 1) / p->b);
   e.entries = nb > 1 ? e.ord_entries() : 0;
@@ -1061,9 +1148,12 @@ resident_kernel(KParams kp) {
   // evaluations per entry: 4^h / n < 4, 2.5 on average over n
   const int passes = lanes ? (e.span * e.entries / lanes * 3 + 6) / (e.span * nb) + 1 : 0;
   int in_span = 0, buf = 0;  // the sweep's place in its span, the span's list buffer
-  bool imp = TASK == kTaskMPI && !p->policy_is_init;
+  bool imp = (TASK == kTaskMPI && !p->policy_is_init) || TASK == kTaskRefine;
   bool first_imp = imp;  // Algorithm 1's initial policy, not an outer iteration
-  bool ending = false;   // VI: the pass that writes the greedy policy
+  bool ending = false;   // VI, correction: the pass that writes the greedy policy
+  // the correction's certificate
+  double residual = NAN, residual_in = NAN, bound = INFINITY;
+  bool fresh = false, done = false;
   int k = 0, kk = 0;     // batch of the sweep, sweep of the evaluation
   if (ordered) e.ord_start(lanes);
   const int kind0 = nb > 1 ? 0 : 1;  // of a sweep's first batch
@@ -1078,6 +1168,7 @@ resident_kernel(KParams kp) {
       if (TASK == kTaskSweep) more = false;
       if (TASK == kTaskVI) more = more && sweeps + 1 < p->max_sweeps;
       if (TASK == kTaskMPI) more = more && kk + 1 < p->K;
+      if (TASK == kTaskRefine) more = more && (p->K ? kk + 1 < p->K : sweeps + 1 < p->max_sweeps);
     }
     // the sweep's list, and the next one's
     const bool span_end = in_span == e.span - 1;
@@ -1097,6 +1188,62 @@ resident_kernel(KParams kp) {
       continue;
     }
     k = 0;
+    if constexpr (TASK == kTaskRefine) {
+      // max|V - J*| <= max|TV - V| / (1 - gamma), and a sweep contracts by gamma
+      const double g = p->gamma, inv = 1.0 / (1.0 - g);
+      const bool ref = p->vref != nullptr;
+      bool stop = false;
+      if (imp) {
+        residual = sh.s_resid;
+        fresh = true;
+        if (ending) break;
+        if (first_imp) {
+          residual_in = residual;
+          bound = residual * inv;
+          if (ref) last_err = e.sweep_err();
+          done = ref ? last_err <= p->eps : bound <= p->eps;
+        } else {
+          ++outer;
+          bound = residual * inv;
+          if (!ref) done = bound <= p->eps;
+        }
+        first_imp = false;
+        if (done || (p->K ? outer >= p->max_outer : p->max_sweeps <= 0) || bad()) break;
+        imp = false;
+        kk = 0;
+      } else {
+        ++t;
+        ++sweeps;
+        if (++in_span == e.span) {
+          in_span = 0;
+          buf ^= 1;
+          if (ordered) e.ord_start(lanes);
+        }
+        fresh = false;
+        last_dv = e.sweep_dv();
+        if (ref) last_err = e.sweep_err();
+        if (p->K == 0) {
+          bound = fmin(g * last_dv * inv, g * bound);
+          done = ref ? last_err <= p->eps : bound <= p->eps;
+          stop = done || sweeps >= p->max_sweeps;
+        } else if (ref && last_err <= p->eps) {
+          done = stop = true;
+        }
+        if (stop) {
+          // the output's residual and greedy policy, when wanted
+          if (!p->policy && p->K == 0) break;
+          ending = true;
+        }
+        if (ending || (p->K && ++kk == p->K)) {
+          imp = true;
+          e.drop_prefetch();
+          b = e.get(2, 0, 0, 0);
+        }
+      }
+      e.dv = e.err = 0.0;
+      __syncthreads();
+      continue;
+    }
     if (TASK == kTaskSweep) {
       sweeps = 1;
       last_dv = e.sweep_dv();
@@ -1146,10 +1293,12 @@ resident_kernel(KParams kp) {
       if (TASK == kTaskMPI || !p->want_policy_out) break;
       ending = true;
     }
-    if (!ending && want_recentre(d)) {
-      if (!e.recentre(gb)) return;
-      ++recentrings;
-      since = 0;
+    if constexpr (TASK != kTaskRefine) {
+      if (!ending && want_recentre(d)) {
+        if (!e.recentre(gb)) return;
+        ++recentrings;
+        since = 0;
+      }
     }
     if (ending || (TASK == kTaskMPI && ++kk == p->K)) {
       imp = true;
@@ -1161,6 +1310,23 @@ resident_kernel(KParams kp) {
     __syncthreads();
   }
   __syncthreads();
+  if constexpr (TASK == kTaskRefine) {
+    for (int s = (int)(blockIdx.x * blockDim.x) + tid; s < n; s += (int)(gridDim.x * blockDim.x))
+      p->vd0[s] = sh.V[s];
+    if (blockIdx.x == 0 && tid == 0) {
+      const double residual_out = fresh ? residual : (double)NAN;
+      Control* ctl = p->ctl;
+      ctl->sweeps = sweeps;
+      ctl->outer_iters = outer;
+      ctl->final_dv_inf = last_dv;
+      ctl->final_err_ref = last_err;
+      ctl->converged = done ? 1 : 0;
+      ctl->residual_in = residual_in;
+      ctl->residual_out = residual_out;
+      ctl->bound_out = p->K > 0 ? residual_out / (1.0 - p->gamma) : bound;
+    }
+    return;
+  }
   // V = W + R into the caller's buffers
   for (int s = (int)(blockIdx.x * blockDim.x) + tid; s < n; s += (int)(gridDim.x * blockDim.x)) {
     const double v = (double)sh.V[Rows::at(s)] + (e.shifted ? p->shift[s] : 0.0);
@@ -1184,6 +1350,8 @@ resident_kernel(KParams kp) {
 // The instantiation for a chunk shape and task.
 template <class T, bool TAIL, int RC, int U, bool NT>
 inline SolveFn resident_task(int task) {
+  if constexpr (T::kType == kF32)
+    if (task == kTaskRefine) return &resident_kernel<T, NT, TAIL, RC, U, kTaskRefine>;
   if (task == kTaskSweep) return &resident_kernel<T, NT, TAIL, RC, U, kTaskSweep>;
   if (task == kTaskVI) return &resident_kernel<T, NT, TAIL, RC, U, kTaskVI>;
   return &resident_kernel<T, NT, TAIL, RC, U, kTaskMPI>;

@@ -1286,10 +1286,9 @@ mbdp_status mdp_refine(mbdp_mdp_t h, double* V, int32_t* policy_out, int32_t K, 
   p.vref = V_ref;
   p.max_sweeps = max_iters;
   p.max_outer = max_iters;
-  if (launch_zero(workspace, w.zero_bytes, stream) != 0)
-    return fail(MBDP_ERR_HIP, "workspace clear failed: %s", hipGetErrorString(hipGetLastError()));
+  p.want_policy_out = policy_out != nullptr;
   char err[256] = {0};
-  if (launch_refine(p, shape_of(h), stream, err, sizeof err) != 0)
+  if (launch_refine(p, w, shape_of(h), stream, err, sizeof err) != 0)
     return fail(MBDP_ERR_HIP, "%s", err);
   Control c;
   st = finish(workspace, stream, &c);
