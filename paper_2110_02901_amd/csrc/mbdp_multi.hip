@@ -40,6 +40,8 @@ namespace mbdp {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 #define MBDP_GLOBAL __attribute__((address_space(1)))
 
@@ -82,37 +84,46 @@ __global__ void __launch_bounds__(256) multi_order_kernel(MultiArgs A, uint64_t 
     A.order[p] = (int32_t)sweep_order_at((uint32_t)p, key);
 }
 
+// LDS-only workgroup barrier: global loads stay in flight across it.
+__device__ __forceinline__ void multi_lds_barrier() {
+  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // Partial products of one K-range: part[split][row][j] = sum over k in the
 // range of code(row, k) * (hi + lo)(k, j).  A wavefront owns 16 RT rows and
 // all NCT * 16 vectors; lane l feeds rows l % 16 of each row tile and vectors
 // l % 16 of each column tile, 8 consecutive k from 8 (l / 16) (the same k map
-// for both operands).  K runs in rounds: the rows come straight from
-// HBM (every load of a round issued before its products), while the W terms
-// of the round, shared by the workgroup's four wavefronts, are staged in LDS
-// once per workgroup with whole-line loads (double buffered: the next
-// round's W is fetched during this round's products).  Reading W per
-// wavefront from L2 in 64-byte pieces cost more than the row stream itself.
-// Rounds are 256 wide for 32 vectors, 128 for 16 and 64 above (measured:
-// wider rounds were slower for 16 and 48 vectors; 64 needs the registers).
+// for both operands).  K runs in rounds: the rows come straight from HBM into
+// one of two register buffers, requested a round before their products, while
+// the W terms, shared by the workgroup's wavefronts, go through LDS (double
+// buffered) by way of registers, requested two rounds before.  So nothing is
+// waited for in the round that requests it, and the workgroup's barriers wait
+// for LDS only.  Reading W per wavefront from L2 in 64-byte pieces cost more
+// than the row stream itself.
 // A row load brings 64 bytes of each of 16 rows (the MFMA operand layout),
 // so each 128-byte line is asked for by two loads of the same wavefront;
 // plain loads, which L1 keeps, serve the second half from the first
 // (non-temporal ones were 1-7% slower).
-template <int RT, int NCT, int ROUND>  // ROUND: K per round (64, 128 or 256)
-__global__ void __launch_bounds__(256) multi_gemm_kernel(MultiArgs A, uint64_t t, int64_t k,
-                                                         int full) {
+// Bound by the row stream: 8192 x 16, b = 1024, r = 32 (268 MB of rows) took
+// 63.1 us a batch with rows and W requested and used in the same round (4.3
+// TB/s), 53.7 with the next round's requested ahead, 52.4 with W two ahead
+// (5.1 TB/s).  Starting the workgroups at different rounds gave 2.5% more but
+// changes the order of the sums.  Wider rounds for 48 and 64 vectors spill.
+template <int RT, int NCT, int ROUND, int NW>  // ROUND: K per round; NW: wavefronts
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+multi_gemm_kernel(MultiArgs A, uint64_t t, int64_t k, int full) {
   constexpr int U = ROUND / 32;
   constexpr int PITCH = ROUND + 8;                     // staged W row, 16-byte pad
   constexpr int PPR = ROUND / 8;                       // 16-byte pieces per staged row
   constexpr int WROWS = 2 * NCT * 16;                  // staged W rows: 2 terms x r vectors
-  constexpr int WPIECES = WROWS * PPR;                 // pieces per round
-  constexpr int WPER = (WPIECES + 255) / 256;          // per thread
+  constexpr int WPER = WROWS * PPR / (64 * NW);        // pieces per thread and round
+  static_assert(WPER * 64 * NW == WROWS * PPR, "");
   __shared__ __attribute__((aligned(16))) uint16_t Wl[2][WROWS][PITCH];
   if (!full && multi_done(A.ctl)) return;  // uniform over the launch
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t kb = k * A.b;
   const int64_t rows = min(A.b, A.n - kb) * A.m;
-  const int64_t wg0 = (int64_t)blockIdx.x * 4 * (16 * RT);
+  const int64_t wg0 = (int64_t)blockIdx.x * NW * (16 * RT);
   if (wg0 >= rows) return;  // whole workgroup: no barrier is skipped by part of it
   const int64_t tile0 = wg0 + wave * (16 * RT);
   const int i = lane & 15, g = lane >> 4;
@@ -134,49 +145,42 @@ __global__ void __launch_bounds__(256) multi_gemm_kernel(MultiArgs A, uint64_t t
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int c = 0; c < NCT; ++c) acc[rt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int64_t k0 = (int64_t)blockIdx.y * A.kchunk;
-  const int64_t k1 = min(n, k0 + A.kchunk);
+  const int k0 = (int)(blockIdx.y * A.kchunk);
+  const int k1 = (int)min(n, (int64_t)k0 + A.kchunk);
   // staged W row w = h * r + j holds W term h of vector j; piece q of a round
-  // is row q / PPR, values 8 (q % PPR) .. +7
-  auto fetch_w = [&](int64_t kk, u32x4 (&wr)[WPER]) {
+  // is row q / PPR, values 8 (q % PPR) .. +7.  The last round may be short:
+  // addresses stay inside the range, what they bring is not used.
+  auto fetch_w = [&](int kk, u32x4 (&wr)[WPER]) {
 #pragma unroll
     for (int e = 0; e < WPER; ++e) {
-      const int q = threadIdx.x + 256 * e;
-      const int w = q / PPR, c8 = (q % PPR) * 8;
-      if (q < WPIECES && kk + c8 < k1) {
-        const int h = w / (NCT * 16), j = w - h * (NCT * 16);
-        wr[e] = *(const MBDP_GLOBAL u32x4*)(Ws + ((size_t)h * A.r + j) * (size_t)n + kk + c8);
-      } else {
-        wr[e] = u32x4{0u, 0u, 0u, 0u};
-      }
+      const int q = threadIdx.x + 64 * NW * e;
+      const int w = q / PPR, c8 = (q % PPR) * 8;  // (Ws is [2][r][n]: w counts its rows)
+      wr[e] = *(const MBDP_GLOBAL u32x4*)(Ws + (size_t)w * (size_t)n + min(kk + c8, k1 - 8));
     }
   };
   auto store_w = [&](int buf, const u32x4 (&wr)[WPER]) {
 #pragma unroll
     for (int e = 0; e < WPER; ++e) {
-      const int q = threadIdx.x + 256 * e;
-      if (q < WPIECES) *(u32x4*)&Wl[buf][q / PPR][(q % PPR) * 8] = wr[e];
+      const int q = threadIdx.x + 64 * NW * e;
+      *(u32x4*)&Wl[buf][q / PPR][(q % PPR) * 8] = wr[e];
     }
   };
-  {
-    u32x4 wr[WPER];
-    fetch_w(k0, wr);
-    store_w(0, wr);
-  }
-  __syncthreads();
-  int buf = 0;
-  for (int64_t kk = k0; kk < k1; kk += ROUND, buf ^= 1) {
-    const int steps = (int)min((int64_t)U, (k1 - kk) / 32);  // last round may be short
-    u32x4 av[U][RT];
+  auto load_a = [&](int kk, u32x4 (&av)[U][RT]) {
+    if (kk + ROUND <= k1) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-        av[u][rt] = u < steps ? *(const MBDP_GLOBAL u32x4*)(arow[rt] + kk + 32 * u)
-                              : u32x4{0u, 0u, 0u, 0u};
-    const bool next = kk + ROUND < k1;
-    u32x4 wr[WPER];
-    if (next) fetch_w(kk + ROUND, wr);
+        for (int rt = 0; rt < RT; ++rt)
+          av[u][rt] = *(const MBDP_GLOBAL u32x4*)(arow[rt] + kk + 32 * u);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          av[u][rt] = *(const MBDP_GLOBAL u32x4*)(arow[rt] + min(kk + 32 * u, k1 - 32));
+    }
+  };
+  auto products = [&](const u32x4 (&av)[U][RT], int buf, int steps) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (u >= steps) break;
@@ -192,9 +196,37 @@ __global__ void __launch_bounds__(256) multi_gemm_kernel(MultiArgs A, uint64_t t
                 0, 0, 0);
         }
     }
-    // the other buffer was last read in the previous round, before its barrier
-    if (next) store_w(buf ^ 1, wr);
-    __syncthreads();
+  };
+  u32x4 A0[U][RT], A1[U][RT], wr[WPER];
+  // One round, with its W in LDS, its rows in `cur` and the next one's W in
+  // wr (both requested a round ago): the next W goes to the other buffer (last
+  // read in the previous round, before its barrier), the W after it and the
+  // next rows are requested, then the products.
+  auto round = [&](int kk, const u32x4 (&cur)[U][RT], u32x4 (&nxt)[U][RT], int buf) {
+    store_w(buf ^ 1, wr);
+    fetch_w(kk + 2 * ROUND, wr);
+    load_a(kk + ROUND, nxt);
+    __builtin_amdgcn_sched_barrier(0);
+    products(cur, buf, U);
+    multi_lds_barrier();
+  };
+  fetch_w(k0, wr);
+  load_a(k0, A0);
+  __builtin_amdgcn_sched_barrier(0);
+  store_w(0, wr);
+  fetch_w(k0 + ROUND, wr);
+  multi_lds_barrier();
+  for (int kk = k0;; kk += 2 * ROUND) {
+    if (kk + ROUND >= k1) {
+      products(A0, 0, (k1 - kk) / 32);
+      break;
+    }
+    round(kk, A0, A1, 0);
+    if (kk + 2 * ROUND >= k1) {
+      products(A1, 1, (k1 - kk - ROUND) / 32);
+      break;
+    }
+    round(kk + ROUND, A1, A0, 1);
   }
   if (tile0 >= rows) return;  // after the last barrier
   // lane l holds rows 4 (l / 16) + v of each 16-row tile, vector l % 16 of each column tile
@@ -325,86 +357,133 @@ __global__ void __launch_bounds__(256) multi_anchor_kernel(MultiArgs A, double* 
   if (mode != 2 && blockIdx.x == 0 && threadIdx.x == 0) A.ctl->w_bound = 0.0;
 }
 
-// PR[row][j] = scale(row) * sum_k code(row, k) R[k][j] in FP64: a workgroup
-// per 64 rows x 64 vectors, K in chunks of 32 through LDS, a 4 x 4 block of
-// outputs per thread.
+// PR[row][j] = scale(row) * sum_k code(row, k) R[k][j] in FP64 on the matrix
+// cores (v_mfma_f64_16x16x4_f64).  A wavefront owns 32 rows and all r vectors;
+// K runs in rounds of 32: lane l feeds codes 8 (l / 16) .. +7 of row l % 16 of
+// each row tile, one 16-byte load for the eight products of the round (product
+// s multiplies the k = 8 (l / 16) + s of either operand), and reads R from the
+// round's copy in LDS (padded so that the two lane groups of a read phase
+// fall on different banks).  Rows, and R two rounds ahead, are requested a
+// round before their use.  Bound by the FP64 rate (r = 32: 69 GFLOP at 8192 x
+// 16, 0.9 ms at the card's nominal 78 TFLOP/s).  4.21 ms with 4 x 4 blocks of
+// vector FMAs of 64 columns whatever r; 1.14 ms here.
+template <int NCT>
 __global__ void __launch_bounds__(256) multi_pr_kernel(MultiArgs A) {
-  __shared__ double Pt[64][33];
-  __shared__ double Rt[32][64];
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  constexpr int RT = 2, r = NCT * 16;
+  constexpr int GP = 8 * r + 16;        // doubles per group of 8 staged R rows
+  constexpr int RPER = 32 * r / 2 / 256;  // 16-byte pieces of R per thread and round
+  __shared__ __attribute__((aligned(16))) double Rt[2][4 * GP];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = lane & 15, g = lane >> 4;
   const int64_t rows = A.n * A.m;
-  const int64_t row0 = (int64_t)blockIdx.x * 64;
-  double acc[4][4];
+  const int n = (int)A.n;
+  const int64_t tile0 = ((int64_t)blockIdx.x * 4 + wave) * (16 * RT);
+  const MBDP_GLOBAL uint16_t* arow[RT];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int rt = 0; rt < RT; ++rt)
+    arow[rt] = (const MBDP_GLOBAL uint16_t*)A.P +
+               (size_t)min(tile0 + rt * 16 + i, rows - 1) * (size_t)n + 8 * g;
+  const MBDP_GLOBAL double* R = (const MBDP_GLOBAL double*)A.R;
+  f64x4 acc[RT][NCT];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[a][c] = 0.0;
-  for (int64_t k0 = 0; k0 < A.n; k0 += 32) {
-    {  // 64 rows x 32 codes: 8 per thread
-      const int lr = tid >> 2, lk = (tid & 3) * 8;
-      const int64_t row = min(row0 + lr, rows - 1);
-      const u32x4 x = *(const u32x4*)(A.P + (size_t)row * A.n + k0 + lk);
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        Pt[lr][lk + 2 * w] = (double)__uint_as_float(x[w] << 16);
-        Pt[lr][lk + 2 * w + 1] = (double)__uint_as_float(x[w] & 0xFFFF0000u);
+    for (int c = 0; c < NCT; ++c) acc[rt][c] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // rounds past the last: addresses stay inside, what they bring is not used
+  auto fetch_r = [&](int k0, f64x2 (&x)[RPER]) {
+    const MBDP_GLOBAL f64x2* src = (const MBDP_GLOBAL f64x2*)(R + (size_t)min(k0, n - 32) * r);
+#pragma unroll
+    for (int e = 0; e < RPER; ++e) x[e] = src[threadIdx.x + 256 * e];
+  };
+  auto store_r = [&](int buf, const f64x2 (&x)[RPER]) {
+#pragma unroll
+    for (int e = 0; e < RPER; ++e) {
+      const int q = 2 * (threadIdx.x + 256 * e);  // of the round's [32][r]
+      *(f64x2*)&Rt[buf][q + 16 * (q / (8 * r))] = x[e];
+    }
+  };
+  auto load_a = [&](int k0, u32x4 (&x)[RT]) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+      x[rt] = *(const MBDP_GLOBAL u32x4*)(arow[rt] + min(k0, n - 32));
+  };
+  f64x2 rr[RPER];
+  u32x4 x[RT], y[RT];
+  fetch_r(0, rr);
+  load_a(0, x);
+  store_r(0, rr);
+  fetch_r(32, rr);
+  multi_lds_barrier();
+  int buf = 0;
+  for (int k0 = 0; k0 < n; k0 += 32, buf ^= 1) {
+    store_r(buf ^ 1, rr);
+    fetch_r(k0 + 64, rr);
+    load_a(k0 + 32, y);
+    __builtin_amdgcn_sched_barrier(0);
+    const double* b0 = &Rt[buf][g * GP + i];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      double bv[NCT];
+#pragma unroll
+      for (int c = 0; c < NCT; ++c) bv[c] = b0[s * r + c * 16];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const unsigned w = x[rt][s / 2];
+        const double av = (double)__uint_as_float(s % 2 ? w & 0xFFFF0000u : w << 16);
+#pragma unroll
+        for (int c = 0; c < NCT; ++c)
+          acc[rt][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[c], acc[rt][c], 0, 0, 0);
       }
     }
-    for (int e = tid; e < 32 * 64; e += 256) {
-      const int kk = e >> 6, j = e & 63;
-      Rt[kk][j] = j < A.r ? A.R[(size_t)(k0 + kk) * A.r + j] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < 32; ++kk) {
-      double a[4], b[4];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) a[x] = Pt[ty * 4 + x][kk];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) b[x] = Rt[kk][tx * 4 + x];
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = fma(a[x], b[y], acc[x][y]);
-    }
-    __syncthreads();
+    for (int rt = 0; rt < RT; ++rt) x[rt] = y[rt];
+    multi_lds_barrier();
   }
+  // lane l holds rows 4 v + l / 16 of each 16-row tile, vector l % 16 of each column tile
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int64_t row = row0 + ty * 4 + x;
-    if (row >= rows) continue;
-    const double sc = (double)A.rscale[row];
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int j = tx * 4 + y;
-      if (j < A.r) A.PR[(size_t)row * A.r + j] = sc * acc[x][y];
+    for (int v = 0; v < 4; ++v) {
+      const int64_t row = tile0 + rt * 16 + 4 * v + g;
+      if (row >= rows) continue;
+      const double sc = (double)A.rscale[row];
+#pragma unroll
+      for (int c = 0; c < NCT; ++c) A.PR[(size_t)row * r + c * 16 + i] = sc * acc[rt][c][v];
     }
-  }
 }
 
 // ------------------------------------------------------------------ launches
 
 typedef void (*MultiGemmFn)(MultiArgs, uint64_t, int64_t, int);
 
-static MultiGemmFn multi_gemm_fn(int32_t r) {
+// The product's instantiation and its wavefronts per workgroup.  Eight share
+// one copy of W where the launch's wavefronts fill the device that way (2048,
+// what the split over K aims at): half the W traffic of four.  Below, four
+// keep more compute units busy.  Per sweep, eight against four (us): 8192 x
+// 16, b = 1024, r = 16 498 / 525, r = 32 555 / 573, r = 64 729 / 782; 2048 x
+// 5, b = 200, r = 16 148 / 141, r = 32 163 / 150, r = 64 243 / 203.  48
+// vectors need more registers than eight wavefronts leave: 906 / 885.
+static MultiGemmFn multi_gemm_fn(int32_t r, int64_t waves, int* nw) {
+  const bool full = waves >= 2048 && r != 48;
+  *nw = full ? 8 : 4;
   switch (r) {
-    case 16: return multi_gemm_kernel<1, 1, 128>;
-    case 32: return multi_gemm_kernel<2, 2, 256>;
-    case 48: return multi_gemm_kernel<3, 3, 64>;
-    case 64: return multi_gemm_kernel<4, 4, 64>;
+    case 16: return full ? multi_gemm_kernel<1, 1, 256, 8> : multi_gemm_kernel<1, 1, 128, 4>;
+    case 32: return full ? multi_gemm_kernel<2, 2, 128, 8> : multi_gemm_kernel<2, 2, 128, 4>;
+    case 48: return multi_gemm_kernel<3, 3, 64, 4>;
+    case 64: return full ? multi_gemm_kernel<4, 4, 64, 8> : multi_gemm_kernel<4, 4, 32, 4>;
     default: return nullptr;
   }
 }
 
-
 int launch_multi_gemm(const MultiArgs& a, uint64_t t, int64_t k, int full, void* stream) {
-  MultiGemmFn f = multi_gemm_fn(a.r);
-  if (!f) return -1;
   const int64_t rows = std::min<int64_t>(a.b, a.n - k * a.b) * a.m;
-  const int64_t per_block = 4 * (int64_t)multi_rows_per_wave(a.r);  // 4 wavefronts
-  const int64_t bx = (rows + per_block - 1) / per_block;
   const int64_t by = (a.n + a.kchunk - 1) / a.kchunk;
-  hipLaunchKernelGGL(f, dim3((unsigned)bx, (unsigned)by), dim3(256), 0,
+  const int64_t tile = multi_rows_per_wave(a.r);
+  int nw = 0;
+  MultiGemmFn f = multi_gemm_fn(a.r, (rows + tile - 1) / tile * by, &nw);
+  if (!f) return -1;
+  const int64_t bx = (rows + nw * tile - 1) / (nw * tile);
+  hipLaunchKernelGGL(f, dim3((unsigned)bx, (unsigned)by), dim3(64 * nw), 0,
                      reinterpret_cast<hipStream_t>(stream), a, t, k, full);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -440,9 +519,12 @@ int launch_multi_anchor(const MultiArgs& a, double* V, int mode, void* stream) {
 }
 
 int launch_multi_pr(const MultiArgs& a, void* stream) {
-  const int64_t blocks = (a.n * a.m + 63) / 64;
-  hipLaunchKernelGGL(multi_pr_kernel, dim3((unsigned)blocks), dim3(256), 0,
-                     reinterpret_cast<hipStream_t>(stream), a);
+  void (*f)(MultiArgs) = a.r == 16   ? multi_pr_kernel<1>
+                         : a.r == 32 ? multi_pr_kernel<2>
+                         : a.r == 48 ? multi_pr_kernel<3>
+                                     : multi_pr_kernel<4>;
+  const int64_t blocks = (a.n * a.m + 127) / 128;  // 32 rows per wavefront
+  hipLaunchKernelGGL(f, dim3((unsigned)blocks), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
