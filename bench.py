@@ -40,7 +40,8 @@ def log(msg):
 # used only while these files are unchanged.
 _KERNEL_SOURCES = {
     "solve": ("mbdp_device.h", "mbdp_engines.h", "mbdp_kernels.hip", "mbdp_kernels_lp_dense.hip",
-              "mbdp_kernels_lp_ell.hip", "mbdp_kernels_lp_band.hip"),
+              "mbdp_kernels_lp_ell.hip", "mbdp_kernels_lp_band.hip", "mbdp_resident.h",
+              "mbdp_resident.hip", "mbdp_resident_lp.hip"),
     "batch": ("mbdp_device.h", "mbdp_engines.h", "mbdp_batch.hip"),
     "multi": ("mbdp_device.h", "mbdp_multi.hip"),
 }

@@ -24,10 +24,10 @@
 //
 // Measured per batch against the workgroup-per-state engine with a grid
 // barrier per batch: 8192 x 16, b = 1024 in FP32 96.3 -> 85.3 us (5.6 -> 6.3 TB/s
-// of rows), in FP8 44.9 -> 25.6 us (3.0 -> 5.2 TB/s); 500 x 6, b = 100 26.4 ->
-// 5.9 us.  Modified policy iteration of 6166 x 4 (b = 512, rows of 4-byte
-// alignment) 104 -> 38.6 ms; one sweep of 64 x 4 108 -> 26.7 us a call; the
-// FP64 correction of 4096 x 8 (b = 512) 19.2 -> 9.6 ms.
+// of rows), in FP8 44.9 -> 25.2 us (3.0 -> 5.3 TB/s); 500 x 6, b = 100 26.4 ->
+// 5.5 us.  Modified policy iteration of 6166 x 4 (b = 512, rows of 4-byte
+// alignment) 104 -> 37.2 ms; one sweep of 64 x 4 108 -> 26.7 us a call; the
+// FP64 correction of 4096 x 8 (b = 512) 19.2 -> 8.9 ms.
 
 #pragma once
 
@@ -565,9 +565,12 @@ struct ResEngine {
   }
 
   // Streams this workgroup's units of the batch, then requests the first two
-  // chunks of `next` (if has_next; not the communicating wavefronts, whose
-  // polling would wait for them).
-  __device__ __forceinline__ void compute(const ResBatch& b, const ResBatch& next, bool has_next) {
+  // chunks of the batch that ahead(next) finds, if it says so (not the
+  // communicating wavefronts, whose polling would wait for them).  Finding it
+  // here keeps its LDS reads and arguments off the path from one exchange to
+  // the next.
+  template <class Ahead>
+  __device__ __forceinline__ void compute(const ResBatch& b, const Ahead& ahead, ResBatch& next) {
     const int r0 = nw - 1 - wave;  // the communicating wavefronts get the last tasks
     for (int u0 = 0; u0 < b.cnt; u0 += b.round) {
       const int units = min(b.round, b.cnt - u0);
@@ -634,6 +637,8 @@ struct ResEngine {
       if (u0 + b.round < b.cnt) lds_barrier();  // the round's LDS is reused
     }
     have = false;
+    refresh();
+    const bool has_next = ahead(next);
     if (has_next && wave >= ncw) {
       const int units = min(next.round, next.cnt);
       const int all = tasks_of(next, units);
@@ -667,36 +672,51 @@ struct ResEngine {
 
   // ---- exchange
 
-  // Words base + j * stride, j < J, of plane h of the phase; false on abort.
-  template <int J>
+  // Words base + j * stride, j < J, of the first H planes of the phase; false
+  // on abort.  (Polls back to back: a pause of 128 cycles between them cost 2%
+  // at 500 x 6, b = 100; a second poll in flight, half a round trip behind,
+  // 4%.)
+  template <int J, int H>
   __device__ __forceinline__ bool fetch(const ResBatch& b, int base, int stride, int limit,
-                                        unsigned long long (&w)[J], int h = 0) {
+                                        unsigned long long (&w)[H][J]) {
     const bool imp = b.mode >= kModeImprove;
     const unsigned want = imp ? (phase & 0x7FFFFFFFu) : (0x800u | (phase & 0x7FFu));
     if (G == 1) {
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const int i = base + j * stride;
-        w[j] = sh.x[h * kResSolo + (i < limit ? i : 0)];
-      }
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const int i = base + j * stride;
+          w[h][j] = sh.x[h * kResSolo + (i < limit ? i : 0)];
+        }
       return true;
     }
-    const unsigned long long* src = words_of(phase) + (size_t)h * n;
-    unsigned long long t0 = 0;
-    for (int spin = 0;; ++spin) {
+    const unsigned long long* src = words_of(phase);
+    const auto request = [&](unsigned long long (&x)[H][J]) {
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const int i = base + j * stride;
+          x[h][j] = atomic_load_agent(src + (size_t)h * n + (i < limit ? i : 0));
+        }
+    };
+    const auto complete = [&](const unsigned long long (&x)[H][J]) {
       bool ok = true;
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const int i = base + j * stride;
-        w[j] = atomic_load_agent(src + (i < limit ? i : 0));
-      }
+      for (int h = 0; h < H; ++h)
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const int i = base + j * stride;
-        const unsigned hi = (unsigned)(w[j] >> 32);
-        ok = ok && (i >= limit || (imp ? hi : hi >> 20) == want);
-      }
-      if (__all(ok)) return true;
+        for (int j = 0; j < J; ++j) {
+          const int i = base + j * stride;
+          const unsigned hi = (unsigned)(x[h][j] >> 32);
+          ok = ok && (i >= limit || (imp ? hi : hi >> 20) == want);
+        }
+      return (bool)__all(ok);
+    };
+    unsigned long long t0 = 0;
+    for (int spin = 0;; ++spin) {
+      request(w);
+      if (complete(w)) return true;
       if (!keep_waiting(spin, t0)) return false;
     }
   }
@@ -711,7 +731,6 @@ struct ResEngine {
         return false;
       }
     }
-    __builtin_amdgcn_s_sleep(2);
     return true;
   }
 
@@ -719,10 +738,16 @@ struct ResEngine {
   template <int J>
   __device__ __forceinline__ bool take(const ResBatch& b, int i0, int stride, int used, int words,
                                        unsigned& changes) {
-    unsigned long long w[J], w2[J];
-    if (!fetch<J>(b, i0 + lane, stride, words, w)) return false;
-    if constexpr (k64) {
-      if (b.mode < kModeImprove && !fetch<J>(b, i0 + lane, stride, words, w2, 1)) return false;
+    unsigned long long v0[kWords][J];
+    unsigned long long (&w)[J] = v0[0];
+    unsigned long long (&w2)[J] = v0[kWords - 1];
+    if (k64 && b.mode >= kModeImprove) {  // one plane only
+      unsigned long long x[1][J];
+      if (!fetch<J, 1>(b, i0 + lane, stride, words, x)) return false;
+#pragma unroll
+      for (int j = 0; j < J; ++j) w[j] = x[0][j];
+    } else if (!fetch<J, kWords>(b, i0 + lane, stride, words, v0)) {
+      return false;
     }
     if (b.mode >= kModeImprove) {
 #pragma unroll
@@ -932,14 +957,15 @@ struct ResEngine {
 
   // ---- a phase
 
-  // One batch or improvement pass: compute, exchange, commit.  `next` (if
-  // has_next) is the batch whose first rows may be requested early.
+  // One batch or improvement pass: compute, exchange, commit.  ahead(next)
+  // finds the batch that follows; true if its first rows may be requested early.
   // order_for: list buffer the order from sweep order_t on is written to, `passes`
   // evaluations of it now or (passes < 0) all that is left; -1: none.
-  __device__ __forceinline__ bool run(const ResBatch& b, const ResBatch& next, bool has_next,
+  template <class Ahead>
+  __device__ __forceinline__ bool run(const ResBatch& b, const Ahead& ahead, ResBatch& next,
                                       bool last, uint64_t order_t, int order_for, int passes,
                                       int lanes) {
-    compute(b, next, has_next);
+    compute(b, ahead, next);
     lds_barrier();  // every unit of this workgroup is published, V is no longer read
     if (wave < ncw) {
       const bool ok = receive(b);
@@ -1159,27 +1185,30 @@ resident_kernel(KParams kp) {
   const int kind0 = nb > 1 ? 0 : 1;  // of a sweep's first batch
   ResBatch b = e.get(imp ? 2 : kind0, 0, 0, 0);
   while (true) {
-    e.refresh();
     const bool last = imp || k == nb - 1;
     e.ncw = imp ? ncw_imp : ncw_sweep;
-    // what follows in the same mode: the next batch, or the first of the next sweep
-    bool more = !imp;
-    if (last) {
-      if (TASK == kTaskSweep) more = false;
-      if (TASK == kTaskVI) more = more && sweeps + 1 < p->max_sweeps;
-      if (TASK == kTaskMPI) more = more && kk + 1 < p->K;
-      if (TASK == kTaskRefine) more = more && (p->K ? kk + 1 < p->K : sweeps + 1 < p->max_sweeps);
-    }
-    // the sweep's list, and the next one's
     const bool span_end = in_span == e.span - 1;
-    const int nx_buf = span_end ? buf ^ 1 : buf, nx_first = span_end ? 0 : (in_span + 1) * e.entries;
-    const bool over = last && !imp;  // the next batch is the next sweep's first
-    const ResBatch nx = e.get(last ? kind0 : (k + 1 == nb - 1 ? 1 : 0), last ? 0 : k + 1,
-                              over ? nx_buf : buf, over ? nx_first : in_span * e.entries);
+    ResBatch nx;
+    // what follows in the same mode: the next batch, or the first of the next sweep
+    const auto ahead = [&](ResBatch& to) {
+      bool more = !imp;
+      if (last) {
+        if (TASK == kTaskSweep) more = false;
+        if (TASK == kTaskVI) more = more && sweeps + 1 < p->max_sweeps;
+        if (TASK == kTaskMPI) more = more && kk + 1 < p->K;
+        if (TASK == kTaskRefine) more = more && (p->K ? kk + 1 < p->K : sweeps + 1 < p->max_sweeps);
+      }
+      // the sweep's list, and the next one's
+      const int nx_buf = span_end ? buf ^ 1 : buf, nx_first = span_end ? 0 : (in_span + 1) * e.entries;
+      const bool over = last && !imp;  // the next batch is the next sweep's first
+      to = e.get(last ? kind0 : (k + 1 == nb - 1 ? 1 : 0), last ? 0 : k + 1,
+                 over ? nx_buf : buf, over ? nx_first : in_span * e.entries);
+      return more;
+    };
     // the next span's order is complete before the last batch of this one
     const bool rest = span_end && k == nb - 2;
     const bool order = ordered && !imp && !(span_end && k == nb - 1);
-    if (!e.run(b, nx, more, last, t + (uint64_t)(e.span - in_span), order ? buf ^ 1 : -1,
+    if (!e.run(b, ahead, nx, last, t + (uint64_t)(e.span - in_span), order ? buf ^ 1 : -1,
                rest ? -1 : passes, lanes))
       return;
     b = nx;
