@@ -7,7 +7,8 @@
 // states of one batch are computed in parallel from the values before the
 // batch and committed together, so later batches see them.  Between batches
 // every workgroup meets at a device-wide barrier (one per batch), instead
-// of one kernel launch per batch.
+// of one kernel launch per batch.  Dense MDPs of up to 16384 states run on
+// the kernel of mbdp_resident.h instead, which has no such barrier.
 //
 // Visibility of V across batches uses two buffers.  In the phase of batch k
 // the kernel reads buffer R (complete up to batch k-1) and writes into the
@@ -16,11 +17,10 @@
 // can therefore read a value of its own batch (Jacobi inside a batch, as
 // eq. (11) requires: M_b(i) holds only earlier batches).  Batches of one
 // sweep are disjoint, but the first batch of sweep t+1 may share states with
-// the last batch of sweep t (all of them when b = n); such states are
-// stamped when the first batch's order is drawn and not copied forward, so
-// the copy can never overwrite their new value.  Stamps live in two arrays
-// by sweep parity: with b = n the next sweep's stamps are written in the
-// same phase that reads the current sweep's.
+// the last batch of sweep t; such states are stamped when the first batch's
+// order is drawn and not copied forward, so the copy can never overwrite
+// their new value.  Stamps live in two arrays by sweep parity.  With b = n
+// every state is written in every phase and nothing is copied.
 //
 // The hot loop is the row gather + dot product Q(s,a) = c(s,a) +
 // gamma * sum_s' P(s,a,s') V(s'):
@@ -30,12 +30,13 @@
 //    workgroups with per-state arrival counters);
 //  * constant row length k (ELL): a wavefront per state, k/4 lanes per row,
 //    one 16-byte load of columns and one of weights per lane, V gathered;
-//  * general CSR: a wavefront per state, lanes striding over each row.
+//  * general CSR: a group of lanes per row by the mean row length.
+// Sparse MDPs of up to 16384 states read V from a copy in LDS.
 // Dot products accumulate in FP32; cost, discount and the action minimum
 // are done in FP64 and the result rounded to FP32.
 //
-// The order of the next batch is computed during the current one and
-// stored, so its ALU work overlaps the memory stream.
+// The order of the next sweep is drawn during the current one and stored, so
+// its ALU work overlaps the memory stream (none at b = n).
 
 #pragma once
 
