@@ -350,8 +350,9 @@ mbdp_status mbdp_permutation(int64_t n, uint64_t seed, uint64_t sweep_index, int
  * minimising action (or mu(s)).  dv_out (device float[1], may be NULL)
  * receives max_s |V_new(s) - V_old(s)|.  Dot products accumulate in FP32;
  * the cost is added and the minimum taken in FP64, then rounded to FP32.
- * Asynchronous; device-side errors (an out-of-range perm entry) are
- * reported by mbdp_sync_status. */
+ * Asynchronous; device-side errors (an out-of-range perm or policy entry) are
+ * reported by mbdp_sync_status.  dv_out is then 0; a bad perm entry leaves V
+ * as it was, a bad policy entry found after the first batch may not. */
 mbdp_status mb_sweep(mbdp_mdp_t h, float* V, const int32_t* policy, int64_t b, uint64_t seed,
                      uint64_t sweep_index, const int32_t* perm, int32_t* argmin_out,
                      float* dv_out, void* workspace, size_t ws_bytes, hipStream_t stream);

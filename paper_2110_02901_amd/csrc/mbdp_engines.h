@@ -1846,7 +1846,10 @@ solve_kernel(KParams p) {
   }
   long long since_recentre = 0;
   if constexpr (!Eng::kBand) d.fill_order(t);
-  if (blockIdx.x == 0 && threadIdx.x == 0) reset_slot(p.ctl, 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    reset_slot(p.ctl, 0);
+    if (p.dv_out) *p.dv_out = 0.f;  // what a failed call leaves
+  }
   if (!grid_sync(d.g)) return;
 
   long long sweeps = 0, outer = 0, changes_last = -1, recentrings = 0;

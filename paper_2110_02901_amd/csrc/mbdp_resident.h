@@ -1093,7 +1093,11 @@ resident_kernel(KParams kp) {
   GridBarrier gb{p->ctl, 0, gridDim.x, p->timeout_ticks};
   uint64_t t = p->first_sweep;
 
-  // prologue: V, the policy, the first sweep's order
+  // prologue: V, the policy, the first sweep's order.  A workgroup that finds a
+  // bad entry of the caller's order or policy leaves before its first batch:
+  // the others wait for its words there and leave too, V untouched.
+  bool bad_entry = false;
+  if (blockIdx.x == 0 && tid == 0 && p->dv_out) *p->dv_out = 0.f;  // what a failed call leaves
   if (gridDim.x == 1 && tid == 0) {  // a lone workgroup clears its own status words
     p->ctl->abort = 0u;
     p->ctl->error = 0u;
@@ -1118,6 +1122,7 @@ resident_kernel(KParams kp) {
       int a = policy_mode ? p->policy[s] : 0;
       if (a < 0 || a >= p->m) {
         raise_abort(p->ctl, kDevBadPolicy);
+        bad_entry = true;
         a = 0;
       }
       sh.pol[s] = (uint16_t)a;
@@ -1136,6 +1141,7 @@ resident_kernel(KParams kp) {
         int v = p->perm[pos];
         if (v < 0 || v >= n) {
           raise_abort(p->ctl, kDevBadPerm);
+          bad_entry = true;
           v = 0;
         }
         sh.list[0][i] = (uint16_t)v;
@@ -1148,16 +1154,16 @@ resident_kernel(KParams kp) {
   } else if (p->perm) {
     // one batch: the order inside it is free, its entries are checked
     for (int i = tid; i < n; i += nt)
-      if (p->perm[i] < 0 || p->perm[i] >= n) raise_abort(p->ctl, kDevBadPerm);
+      if (p->perm[i] < 0 || p->perm[i] >= n) {
+        raise_abort(p->ctl, kDevBadPerm);
+        bad_entry = true;
+      }
   }
-  __syncthreads();
+  if (__syncthreads_or(bad_entry)) return;
 
   long long sweeps = 0, outer = 0, changes_last = -1, recentrings = 0, since = 0;
   double last_dv = NAN, last_err = NAN;
   int converged = 0;
-  const auto bad = [&]() {  // an error raised by any workgroup ends the call
-    return __hip_atomic_load(&p->ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  };
   const auto want_recentre = [&](double d) {
     ++since;
     if (p->recentre_every <= 0 || since < p->recentre_every) return false;
@@ -1237,7 +1243,7 @@ resident_kernel(KParams kp) {
           if (!ref) done = bound <= p->eps;
         }
         first_imp = false;
-        if (done || (p->K ? outer >= p->max_outer : p->max_sweeps <= 0) || bad()) break;
+        if (done || (p->K ? outer >= p->max_outer : p->max_sweeps <= 0)) break;
         imp = false;
         kk = 0;
       } else {
@@ -1293,7 +1299,6 @@ resident_kernel(KParams kp) {
         }
         if (outer >= p->max_outer) break;
       }
-      if (bad()) break;
       first_imp = false;
       kk = 0;
       __syncthreads();  // the statistics are read before they are written again
