@@ -1099,9 +1099,10 @@ resident_kernel(KParams kp) {
   bool bad_entry = false;
   if (blockIdx.x == 0 && tid == 0 && p->dv_out) *p->dv_out = 0.f;  // what a failed call leaves
   if (gridDim.x == 1 && tid == 0) {  // a lone workgroup clears its own status words
-    p->ctl->abort = 0u;
-    p->ctl->error = 0u;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), before any error is raised
+    store_shared(&p->ctl->abort, 0u);
+    store_shared(&p->ctl->error, 0u);
+    // performed before any error is raised (after the workgroup barrier below)
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   for (int i = tid; i < kResQ; i += nt) sh.cnt[i] = 0u;
   if (tid == 0) {

@@ -65,3 +65,18 @@ def test_sparse_order(k):
         wrong = np.arange(n, dtype=np.int32)
         wrong[-1] = n
         check_left_alone(h, n, b, perm=up(wrong))
+
+
+@pytest.mark.parametrize("n,b", [(40, 10), (1500, 300)])
+def test_status_words_of_another_call(n, b):
+    # a workspace of ones: an abort and an error that no call of ours raised
+    P, c = inputs.dense_mdp(n, 3, 0.5, 9, dtype=np.float32)
+    h, _ = dense_case(P, c, 0.9)
+    ws = mb.workspace(h, b)
+    V = torch.zeros(n, device=dev())
+    for t in range(5):
+        ws.fill_(0xFF)
+        mb.mb_sweep(h, V, b, 3, t, ws)
+        mb.mbdp_sync_status(ws)
+    ws.fill_(0xFF)
+    assert mb.vi_solve(h, V, b, 3, ws, tol_dv=1e-6)["converged"]
