@@ -98,6 +98,7 @@ struct BatchShared {
   double V[kBatchMaxN];
   double newv[kBatchMaxB];            // a lone workgroup's new values of the batch
   uint16_t order[2][kBatchMaxN];      // sigma_t, by sweep parity
+  double zero[16];                    // V of the columns past a row's end
   double red[16];
   int item, rank, ok;
 };
@@ -200,7 +201,7 @@ struct BatchSolver {
   __device__ __forceinline__ void consume(int st, const Buf& f, double (&acc)[R]) const {
     const int j = (st * LANES + sl) * EPL;
     const bool in = j < ld;
-    const double* vp = sh.V + (in ? j : 0);
+    const double* vp = in ? sh.V + j : sh.zero;
     double v[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) v[e] = vp[e];
@@ -368,6 +369,7 @@ struct BatchSolver {
     double* gnew = A.team_new + (size_t)I.slot * 2 * kBatchMaxB;    // [2][kBatchMaxB]
     const MBDP_GLOBAL double* V0 = gview<double>(I.V);
     for (int j = (int)threadIdx.x; j < ld; j += (int)blockDim.x) sh.V[j] = j < n ? V0[j] : 0.0;
+    if (threadIdx.x < 16) sh.zero[threadIdx.x] = 0.0;
     draw_order(0);
     __syncthreads();
     const unsigned long long t_start = wall_clock64();
