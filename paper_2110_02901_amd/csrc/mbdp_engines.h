@@ -94,8 +94,9 @@ struct RegAcc {
     changes = 0;
   }
   __device__ __forceinline__ void max_abs(int i, double x) { v[i] = fmax(v[i], x); }
-  __device__ __forceinline__ void range(float w) {
-    wabs = max(wabs, __float_as_uint(w) & 0x7FFFFFFFu);
+  __device__ __forceinline__ void range(float w) {  // NaN is ignored, as by fmax
+    const unsigned x = __float_as_uint(w) & 0x7FFFFFFFu;
+    wabs = max(wabs, x > 0x7F800000u ? 0u : x);
   }
   __device__ __forceinline__ void count_change() { changes += 1; }
 
@@ -155,7 +156,7 @@ struct LdsAcc {
     if (x == x) atomicMax(&a[i], (unsigned long long)__double_as_longlong(x));
   }
   __device__ __forceinline__ void range(float w) {
-    atomicMax(&a[kAccWabs], (unsigned long long)__double_as_longlong((double)fabsf(w)));
+    if (w == w) atomicMax(&a[kAccWabs], (unsigned long long)__double_as_longlong((double)fabsf(w)));
   }
   __device__ __forceinline__ void count_change() { atomicAdd(&a[kAccChanges], 1ull); }
 

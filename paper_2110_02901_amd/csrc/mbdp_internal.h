@@ -26,7 +26,7 @@ enum Acc : int {
   kAccDv = 0,      // max |W_new - W_old|
   kAccErr = 1,     // max |W_new + r - V_ref|
   kAccResid = 2,   // max |TW - W|
-  kAccWabs = 3,    // max |W_new| (a NaN counts as larger than any value)
+  kAccWabs = 3,    // max |W_new| (NaN ignored)
   kAccChanges = 4, // policy changes (count)
   kNumAcc = 5
 };
