@@ -480,7 +480,9 @@ constexpr int kMaxActions = 1024;
 template <int R, int VEC, class T = ValF32>
 struct DenseEngine {
   static constexpr bool kBand = false;
-  static constexpr bool kPlainStores = true, kCoherent = false;  // (of the split counters)
+  static constexpr bool kCoherent = false;
+  // (the split partials and counters)
+  __device__ __forceinline__ static bool plain(const KParams&, int) { return true; }
   __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
   using Acc = LdsAcc;
   // 16-byte row loads in flight per thread and step: 16 for FP32 and BF16;
@@ -737,7 +739,8 @@ __device__ __forceinline__ const float* stage_values(const float* rd, int64_t n)
 template <int UNR, int LPR, class T = ValF32, bool LDSV = false>
 struct EllEngine {
   static constexpr bool kBand = false;
-  static constexpr bool kPlainStores = false, kCoherent = LDSV;
+  static constexpr bool kCoherent = LDSV;
+  __device__ __forceinline__ static bool plain(const KParams&, int) { return false; }
   __device__ __forceinline__ static bool coherent(const KParams&, int) { return LDSV; }
   using Acc = RegAcc;
 
@@ -1359,7 +1362,8 @@ __device__ __forceinline__ float lane_group_sum(float v) {
 template <int LPG, bool LDSV = false>
 struct CsrEngine {
   static constexpr bool kBand = false;
-  static constexpr bool kPlainStores = false, kCoherent = true;
+  static constexpr bool kCoherent = true;
+  __device__ __forceinline__ static bool plain(const KParams&, int) { return false; }
   using Acc = RegAcc;
   static constexpr int kRows = 4;  // rows of a group in flight
   static constexpr int kEnt = 2;   // entries of a row per lane and pass
@@ -1659,7 +1663,7 @@ struct Driver {
       prev_count = bord ? bk : 0;
       const bool end = k == nb - 1;
       if (end) L.flush(p.ctl, slot(), false, p.vref != nullptr);
-      if (!grid_sync(g, Eng::kPlainStores, !coh, end ? slot() : -1)) return false;
+      if (!grid_sync(g, Eng::plain(p, mode), !coh, end ? slot() : -1)) return false;
       ++phase;
     }
     ++epoch;
@@ -1747,7 +1751,7 @@ struct Driver {
     CtxT<VT> c{rd_buf(), wr_buf()};
     Eng::template batch<CE, true>(p, nullptr, p.n, c, count ? kModeImproveCount : kModeImprove, L);
     L.flush(p.ctl, slot(), true, p.vref != nullptr);
-    if (!grid_sync(g, Eng::kPlainStores, true, slot())) return false;
+    if (!grid_sync(g, Eng::plain(p, kModeImprove), true, slot())) return false;
     ++epoch;
     return true;
   }

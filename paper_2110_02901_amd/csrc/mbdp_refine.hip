@@ -44,10 +44,13 @@ namespace mbdp {
 namespace {
 
 // New value q (action a) of state s in a sweep.
-template <class Acc>
+template <bool PLAIN, class Acc>
 __device__ __forceinline__ void commit64(const KParams& p, const CtxT<double>& c, int32_t s,
                                          double q, int a, double old, Acc& L) {
-  store_shared(&c.wr[s], q);
+  if constexpr (PLAIN)
+    c.wr[s] = q;
+  else
+    store_shared(&c.wr[s], q);
   if (p.argmin_out) p.argmin_out[s] = a;
   L.max_abs(kAccDv, fabs(q - old));
   if (p.vref) L.max_abs(kAccErr, fabs(q - p.vref[s]));
@@ -55,12 +58,15 @@ __device__ __forceinline__ void commit64(const KParams& p, const CtxT<double>& c
 
 // Improvement step at state s (V fixed): the residual |(TV)(s) - V(s)|, the
 // greedy action, and the error of V(s) itself against V_ref.
-template <class Acc>
+template <bool PLAIN, class Acc>
 __device__ __forceinline__ void improve64(const KParams& p, int32_t s, double q, int a,
                                           double old, bool count, Acc& L) {
   if (p.policy) {
     if (count && p.policy[s] != a) L.count_change();
-    store_shared(&p.policy[s], a);
+    if constexpr (PLAIN)
+      p.policy[s] = a;
+    else
+      store_shared(&p.policy[s], a);
   }
   L.max_abs(kAccResid, fabs(q - old));
   if (p.vref) L.max_abs(kAccErr, fabs(old - p.vref[s]));
@@ -103,8 +109,9 @@ __device__ __forceinline__ Dense64Shared& dense64_shared() {
 template <int VEC>
 struct Dense64Engine {
   static constexpr bool kBand = false;
-  static constexpr bool kPlainStores = false, kCoherent = false;
+  static constexpr bool kCoherent = false;
   __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
+  __device__ __forceinline__ static bool plain(const KParams&, int) { return false; }
   using Acc = LdsAcc;
   static constexpr int R = 8;   // rows of a state per pass
   static constexpr int U = 1;   // column steps in flight (R * U 16-byte loads per thread)
@@ -206,9 +213,9 @@ struct Dense64Engine {
         if (lane == 0) {
           const double old = c.rd[s];
           if (mode >= kModeImprove)
-            improve64(p, s, qv, av, old, mode == kModeImproveCount, L);
+            improve64<false>(p, s, qv, av, old, mode == kModeImproveCount, L);
           else
-            commit64(p, c, s, qv, av, old, L);
+            commit64<false>(p, c, s, qv, av, old, L);
         }
       }
       __syncthreads();
@@ -271,7 +278,8 @@ struct Dense64Engine {
         }
       }
       acc = wave_sum_d(acc);
-      if (lane == 0) commit64(p, c, s, (double)p.c32[row] + p.gamma * acc, a, c.rd[s], L);
+      if (lane == 0)
+        commit64<false>(p, c, s, (double)p.c32[row] + p.gamma * acc, a, c.rd[s], L);
     }
   }
 
@@ -292,10 +300,23 @@ struct Dense64Engine {
 template <int LPR>
 struct Ell64Engine {
   static constexpr bool kBand = false;
-  static constexpr bool kPlainStores = false, kCoherent = false;
+  static constexpr bool kCoherent = false;
   __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
   using Acc = RegAcc;
   static constexpr int kRpp = kWave / LPR;  // rows per wavefront pass
+  // Whether a batch is committed with plain stores, which its barrier then
+  // releases (~1.7 us): a store through to memory is waited for with the next
+  // unit's loads, so it pays only where a wavefront has one unit or the unit
+  // is long.  5 policy sweeps and an improvement pass, m = 2, k = 32, stored
+  // through / plain: 10^6 states, b = 250 000 4.70 / 3.19 ms; 10^5 (m = 4),
+  // b = n 471 / 289 us; 16 384, b = 256 (one unit) 3.59 / 4.06 ms.  Minimum
+  // sweeps serve a state's m rows per unit: 16 384 states, b = 8192 33 / 38 us,
+  // 10^6 the same either way.
+  __device__ __forceinline__ static bool plain(const KParams& p, int mode) {
+    if (mode == kModeMin) return false;
+    const int64_t units = mode == kModePolicy ? (p.b + kRpp - 1) / kRpp : p.n;
+    return units > (int64_t)gridDim.x * (blockDim.x >> 6);
+  }
 
   // FP64 dot product of this lane's (up to) 4 entries at entry e with V,
   // summed over the LPR lanes of the row (every lane of the group gets it).
@@ -317,6 +338,15 @@ struct Ell64Engine {
   template <bool CE, bool IDENT, class Acc>
   __device__ __forceinline__ static void batch(const KParams& p, const int32_t* ord, int64_t bk,
                                                const CtxT<double>& c, int mode, Acc& L) {
+    if (plain(p, mode))
+      run<IDENT, true>(p, ord, bk, c, mode, L);
+    else
+      run<IDENT, false>(p, ord, bk, c, mode, L);
+  }
+
+  template <bool IDENT, bool PLAIN, class Acc>
+  __device__ __forceinline__ static void run(const KParams& p, const int32_t* ord, int64_t bk,
+                                             const CtxT<double>& c, int mode, Acc& L) {
     const int m = p.m, k = p.ell_k;
     const int lane = threadIdx.x & 63, g = lane / LPR, l = lane % LPR;
     const bool has = l * 4 < k;
@@ -336,7 +366,8 @@ struct Ell64Engine {
         }
         const int64_t row = (int64_t)s * m + a;
         const double part = row_part(p, (size_t)row * k + lcol, has, V);
-        if (l == 0 && valid) commit64(p, c, s, (double)p.c32[row] + p.gamma * part, a, V[s], L);
+        if (l == 0 && valid)
+          commit64<PLAIN>(p, c, s, (double)p.c32[row] + p.gamma * part, a, V[s], L);
       }
       return;
     }
@@ -363,9 +394,9 @@ struct Ell64Engine {
       if (lane == 0) {
         const int av = ab == 0x7fffffff ? 0 : ab;
         if (mode >= kModeImprove)
-          improve64(p, s, qb, av, V[s], mode == kModeImproveCount, L);
+          improve64<PLAIN>(p, s, qb, av, V[s], mode == kModeImproveCount, L);
         else
-          commit64(p, c, s, qb, av, V[s], L);
+          commit64<PLAIN>(p, c, s, qb, av, V[s], L);
       }
     }
   }
@@ -375,8 +406,15 @@ struct Ell64Engine {
 
 struct Csr64Engine {
   static constexpr bool kBand = false;
-  static constexpr bool kPlainStores = false, kCoherent = false;
+  static constexpr bool kCoherent = false;
   __device__ __forceinline__ static bool coherent(const KParams&, int) { return false; }
+  // As for rows of constant length, from more than two states a wavefront on
+  // (16 384 states, m = 2, rows of 1 to 40 entries: b = 8192, two states,
+  // 172 us through, 193 plain; b = n, four states, 149 and 136).
+  __device__ __forceinline__ static bool plain(const KParams& p, int mode) {
+    const int64_t states = mode == kModePolicy ? p.b : p.n;
+    return mode != kModeMin && states > 2 * (int64_t)gridDim.x * (blockDim.x >> 6);
+  }
   using Acc = RegAcc;
 
   __device__ __forceinline__ static double row_dot(const KParams& p, int64_t row,
@@ -391,6 +429,15 @@ struct Csr64Engine {
   template <bool CE, bool IDENT, class Acc>
   __device__ __forceinline__ static void batch(const KParams& p, const int32_t* ord, int64_t bk,
                                                const CtxT<double>& c, int mode, Acc& L) {
+    if (plain(p, mode))
+      run<IDENT, true>(p, ord, bk, c, mode, L);
+    else
+      run<IDENT, false>(p, ord, bk, c, mode, L);
+  }
+
+  template <bool IDENT, bool PLAIN, class Acc>
+  __device__ __forceinline__ static void run(const KParams& p, const int32_t* ord, int64_t bk,
+                                             const CtxT<double>& c, int mode, Acc& L) {
     const int m = p.m;
     const int lane = threadIdx.x & 63;
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -411,7 +458,8 @@ struct Csr64Engine {
         }
         const int64_t row = (int64_t)s * m + a;
         const double part = row_dot(p, row, V);
-        if (lane == 0) commit64(p, c, s, (double)p.c32[row] + p.gamma * part, a, V[s], L);
+        if (lane == 0)
+          commit64<PLAIN>(p, c, s, (double)p.c32[row] + p.gamma * part, a, V[s], L);
         continue;
       }
       double qb = INFINITY;
@@ -426,9 +474,9 @@ struct Csr64Engine {
       }
       if (lane == 0) {
         if (mode >= kModeImprove)
-          improve64(p, s, qb, ab, V[s], mode == kModeImproveCount, L);
+          improve64<PLAIN>(p, s, qb, ab, V[s], mode == kModeImproveCount, L);
         else
-          commit64(p, c, s, qb, ab, V[s], L);
+          commit64<PLAIN>(p, c, s, qb, ab, V[s], L);
       }
     }
   }
