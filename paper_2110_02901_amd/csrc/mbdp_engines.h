@@ -1444,11 +1444,12 @@ struct CsrEngine {
           float part[kRows];
 #pragma unroll
           for (int q = 0; q < kRows; ++q) {
-            const int r = min(r0 + q * groups, nr - 1);
+            const bool in = r0 + q * groups < nr;  // (a slot past the rows has none)
+            const int r = in ? r0 + q * groups : nr - 1;
             const int i = r / pr;
             const int64_t row = (int64_t)sh.s[i] * m + sh.a[i] + a0 + (r - i * pr);
             e0[q] = p.row_ptr[row] + l;
-            e1[q] = p.row_ptr[row + 1];
+            e1[q] = in ? p.row_ptr[row + 1] : 0;
             cost[q] = cost_of<CE>(p, row);
             part[q] = 0.f;
           }
