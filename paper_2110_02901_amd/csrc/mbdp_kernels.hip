@@ -6,6 +6,8 @@
 #include <math.h>
 #include <stdio.h>
 
+#include <algorithm>
+
 #include "mbdp_engines.h"
 
 namespace mbdp {
@@ -419,8 +421,7 @@ static bool band_fits(const KParams& p, int blocks) {
 // and the memory-side cache): read with plain loads; larger ones with
 // non-temporal loads, which left the caches to V and ran 8% faster.
 constexpr int64_t kResCachedBytes = (int64_t)64 << 20;
-constexpr int64_t kResSoloStates = 1024;        // one workgroup: states,
-constexpr int64_t kResSoloBatch = 128 << 10;    // and row bytes of a batch
+constexpr int64_t kResSoloStates = 1024;  // a lone workgroup's words of a batch (LDS)
 
 static int grid_blocks(SolveFn f, const LaunchShape& shape, int* blocks, char* err,
                        size_t errlen) {
@@ -464,10 +465,34 @@ bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blocks) {
   if (g > p.n) g = (int)p.n;
   const bool policy = p.task == kTaskMPI || (p.task == kTaskSweep && p.policy_sweep) ||
                       (p.task == kTaskRefine && p.K > 0);
-  // one workgroup where a batch is so short that the exchange between
-  // workgroups would cost more than its rows
-  const int64_t batch_bytes = p.b * p.m * p.n * wb;
-  if (p.n <= kResSoloStates && batch_bytes <= kResSoloBatch) g = 1;
+  // One workgroup where its rows cost less than what it saves, the exchange of
+  // each batch and, for a single sweep, the cooperative launch and the clear
+  // before it (~16 us).  Microseconds, one workgroup / all:
+  //  * a single sweep: alone a batch takes 1/30 us more per row, or per 1.3 KB
+  //    of them, and saves 2.2: 64 x 4, b = 16 30 / 44, b = 64 25 / 34; 500 x 4,
+  //    b = 8 237 / 288; 64 x 16, b = 8 78 / 61; up to 128 KB (256 x 2,
+  //    b = n, 512 KB, 42 / 35);
+  //  * minimum sweeps of a solve, per sweep: up to 32 rows (4 a wavefront) and
+  //    64 KB: 8 x 4, b = 8 6.6 / 7.8; 1024 x 8, b = 1 3302 / 4353; 64 x 4, b = 16
+  //    24 / 18; 1000 x 4, b = 8 1048 / 560; 256 x 8, b = 16 141 / 75; in FP64
+  //    32 KB: 1000 x 1, b = 8 484 / 505, b = 16 322 / 264;
+  //  * policy sweeps of a solve, whose improvement passes take every row, per
+  //    5 sweeps and a pass: up to 8 KB of a batch's actions: 64 x 4, b = 4 0.95
+  //    of the time of all, 500 x 4, b = 4 3089 / 2349.
+  const bool improves = p.task == kTaskMPI || (p.task == kTaskRefine && p.K > 0);
+  const int64_t rows = p.b * (p.task == kTaskSweep && p.policy_sweep ? 1 : p.m);
+  const int64_t batch_bytes = rows * p.n * wb;
+  bool alone = batch_bytes <= (128 << 10);
+  if (p.task == kTaskSweep) {
+    const double batches = (double)((p.n + p.b - 1) / p.b);
+    const double more = std::max((double)rows / 30.0, (double)batch_bytes / 38e3);
+    alone = alone && batches * more <= 2.2 * batches + 16.0;
+  } else if (improves) {
+    alone = batch_bytes <= (8 << 10);
+  } else {
+    alone = rows <= 32 && batch_bytes < (p.task == kTaskRefine ? 32 << 10 : 64 << 10);
+  }
+  if (p.n <= kResSoloStates && alone) g = 1;
   // A position's rows are split into a power of two of parts where that
   // shortens the longest share of a batch (few positions per workgroup);
   // an argmin output needs all rows of a state in one place.
@@ -476,9 +501,9 @@ bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blocks) {
     int64_t best = (p.b + g - 1) / g * p.m;
     for (int lg = 1; lg <= 6 && (1 << lg) <= p.m; ++lg) {
       if ((p.b << lg) > p.n) break;
-      const int64_t rows = ((p.b << lg) + g - 1) / g * ((p.m + (1 << lg) - 1) >> lg);
-      if (rows < best) {
-        best = rows;
+      const int64_t longest = ((p.b << lg) + g - 1) / g * ((p.m + (1 << lg) - 1) >> lg);
+      if (longest < best) {
+        best = longest;
         p.res_lgp = lg;
       }
     }
