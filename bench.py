@@ -885,7 +885,8 @@ def run_single(args, dev, wl_name):
             "unit": "GB/s",
             "frac": kernel_gbps / HBM_PEAK_GBPS,
             "traffic": traffic,
-            "kernel": "solve_kernel, %s engine, VI (one launch per solve)" % engine,
+            "kernel": ("resident_kernel, VI (one launch per solve)" if dense and n <= 16384 else
+                       "solve_kernel, %s engine, VI (one launch per solve)" % engine),
             "algorithmic_bytes_per_backup": bytes_per_backup,
         },
     }

@@ -310,12 +310,14 @@ mbdp_status mdp_set_tuning(mbdp_mdp_t h, const mbdp_tuning* t);
 size_t mdp_workspace_bytes(mbdp_mdp_t h, int64_t b);
 
 /* Name of the kernel family that mb_sweep (without an explicit order),
- * vi_solve and mpi_solve run for this handle and batch size b: "dense",
+ * vi_solve and mpi_solve run for this handle and batch size b: "dense" (V in
+ * every workgroup's LDS up to 16384 states, else a workgroup per state),
  * "ell" (constant row length, V gathered from memory), "ell-band" (constant
  * row length with every column within a band around its state: each
  * workgroup owns a chunk of states and stages the band of V it reads in
- * LDS), "ell-colblock" (b = n with column blocks attached) or "csr".  The choice follows the handle's tuning.  *name points to
- * a static string.  No device work. */
+ * LDS), "ell-colblock" (b = n with column blocks attached) or "csr".  The
+ * choice follows the handle's tuning.  *name points to a static string.  No
+ * device work. */
 mbdp_status mdp_engine(mbdp_mdp_t h, int64_t b, const char** name);
 
 /* Optional input checks: P entries in [0, inf), FP64 row sums within
@@ -365,8 +367,10 @@ mbdp_status mbdp_sync_status(void* workspace, size_t ws_bytes, hipStream_t strea
  * IV-A), apply sweeps t = first_sweep, first_sweep + 1, ... of B_b with
  * order sigma_t until max|V_{t+1} - V_t| <= tol_dv (tol_dv < 0 disables),
  * or -- when V_ref (device FP64[n]) is given -- max|V_{t+1} - V_ref| <= eps,
- * or max_sweeps sweeps.  All sweeps run in one persistent kernel launch
- * with a device-wide barrier between batches.
+ * or max_sweeps sweeps.  All sweeps run in one persistent kernel launch;
+ * between batches its workgroups exchange the new values (dense, up to 16384
+ * states), wait for the workgroups whose states they read (banded) or meet
+ * at a device-wide barrier.
  * Precision: the iterate is kept as V = W + R with W in FP32 and an FP64
  * anchor R, iterating W with the costs c(s,a) - R(s) + gamma (P R)(s,a);
  * this is exact in real arithmetic for any order and batch size.  Whenever

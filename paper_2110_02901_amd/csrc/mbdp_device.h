@@ -1,5 +1,5 @@
-// Device building blocks of libmbdp: the sweep order, the grid barrier,
-// wavefront reductions and order-preserving keys for atomic max/min.
+// Device building blocks of libmbdp: the sweep order, wavefront reductions,
+// stores and loads past the caches, the grid barrier.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -118,12 +118,6 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 __device__ __forceinline__ double wave_max_d(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  return v;
-}
-
-__device__ __forceinline__ double wave_min_d(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
   return v;
 }
 

@@ -31,7 +31,7 @@
 //  * constant row length k (ELL): a wavefront per state, k/4 lanes per row,
 //    one 16-byte load of columns and one of weights per lane, V gathered;
 //  * general CSR: a group of lanes per row by the mean row length.
-// Sparse MDPs of up to 16384 states read V from a copy in LDS.
+// FP32 sparse MDPs of up to 16384 states read V from a copy in LDS.
 // Dot products accumulate in FP32; cost, discount and the action minimum
 // are done in FP64 and the result rounded to FP32.
 //
@@ -700,9 +700,13 @@ struct DenseEngine {
 
 // ------------------------------------------------------------ V in LDS
 //
-// Sparse MDPs of at most kLdsStates states: every workgroup copies V into LDS
-// at the start of a phase (agent-coherent loads, 64 KB at most), so the
-// gathers are LDS reads and the barriers need neither fence.
+// FP32 sparse MDPs of at most kLdsStates states: every workgroup copies V into
+// LDS at the start of a phase (agent-coherent loads, 64 KB at most), so the
+// gathers are LDS reads and the barriers need neither fence.  The limit is the
+// size that was built and measured, not one the LDS forces; the copy pays for
+// large batches.  Value iteration, m = 8, rows of 1 to 40 entries, us a sweep at
+// 16384 states (in LDS) / 16400 (from memory): b = n 23 / 28, 4096 53 / 75, 1024
+// 155 / 151, 256 567 / 462.  BF16 and FP8 rows gather from memory at any size.
 constexpr int kLdsStates = 16384;
 
 __device__ __forceinline__ float* lds_values() {
@@ -1331,7 +1335,7 @@ struct ColEngine : EllEngine<UNR, LPR, ValF32> {
 // Rows of any length.  The rows of a workgroup's states (its positions of the
 // batch, every gridDim-th) go to groups of LPG lanes, kRows rows of a group at
 // a time, so that the chain row pointer -> column and value -> V(column) of
-// one row is not waited for alone; LPG is about half the mean row length.
+// one row is not waited for alone; LPG by the mean row length.
 // Each row's Q goes to LDS, then a thread per state takes the minimum and
 // commits.  Bound by the chain of dependent loads (order, policy, row pointer,
 // column, V) and the barrier.  MPI at n = 50 000, m = 5, rows of 1 to 40

@@ -364,7 +364,14 @@ static SolveFn pick(const KParams& p, int units_per_wave_hint) {
       default: return two ? solve_fn<EllEngine<2, 64>>(p.task) : solve_fn<EllEngine<1, 64>>(p.task);
     }
   }
-  // lanes per row: about half the mean row length (rounded to a power of two)
+  // Lanes per row by the mean row length.  Times of 4 / 8 / 32 / 64 lanes over
+  // the best of any width (with 16), averaged over value and modified policy
+  // iteration of 10 000, 50 000 and 500 000 states at three batch sizes: mean 5
+  // 1.03 / 1.00 / 1.12 / 1.35, 10 1.07 / 1.02 / 1.07 / 1.26, 20 1.13 / 1.04 / 1.03
+  // / 1.13, 28 1.20 / 1.07 / 1.02 / 1.10, 60 1.40 / 1.16 / 1.02 / 1.03, 100 1.57 /
+  // 1.24 / 1.03 / 1.01, 200 1.90 / 1.40 / 1.06 / 1.00.  (16 lanes, not built: 1.00
+  // to 1.02 from 8 to 45.)  The lines were drawn before slots past a round's rows
+  // were empty and lie within 5% of the best of the four.
   const int64_t len = p.nnz / (p.n * p.m);
   if (p.n <= kLdsStates) {
     if (len <= 10) return solve_fn<CsrEngine<4, true>>(p.task);

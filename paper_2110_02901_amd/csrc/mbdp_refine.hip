@@ -22,7 +22,7 @@
 //    FP64 V in LDS, two tagged words per value in the exchange.  Against the
 //    engine below with V staged in LDS per batch (a workgroup per state, two
 //    workgroup barriers per 8 rows, a grid barrier per batch) 4096 x 8,
-//    b = 512, went from 19.2 to 8.9 ms a correction (5.0 ms of rows at
+//    b = 512, went from 19.2 to 8.6 ms a correction (5.0 ms of rows at
 //    6.5 TB/s);
 //  * dense, larger (V does not fit in LDS) or with rows shorter than a load:
 //    a workgroup per state streams the state's m rows (8 rows at a time, one

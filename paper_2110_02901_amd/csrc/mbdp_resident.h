@@ -25,9 +25,9 @@
 // Measured per batch against the workgroup-per-state engine with a grid
 // barrier per batch: 8192 x 16, b = 1024 in FP32 96.3 -> 85.3 us (5.6 -> 6.3 TB/s
 // of rows), in FP8 44.9 -> 25.2 us (3.0 -> 5.3 TB/s); 500 x 6, b = 100 26.4 ->
-// 5.5 us.  Modified policy iteration of 6166 x 4 (b = 512, rows of 4-byte
-// alignment) 104 -> 37.2 ms; one sweep of 64 x 4 108 -> 26.7 us a call; the
-// FP64 correction of 4096 x 8 (b = 512) 19.2 -> 8.9 ms.
+// 5.3 us.  Modified policy iteration of 6166 x 4 (b = 512, rows of 4-byte
+// alignment) 104 -> 37.6 ms; one sweep of 64 x 4 108 -> 26 us a call; the
+// FP64 correction of 4096 x 8 (b = 512) 19.2 -> 8.6 ms.
 
 #pragma once
 

@@ -731,8 +731,11 @@ mbdp_status mdp_batch_upload(const mbdp_batch_item* items, int32_t count, void* 
     return (int32_t)std::min<int64_t>(kBatchMaxTeam, std::max<int64_t>(1, (b.b + groups - 1) / groups));
   };
   if (count <= cus && cus >= 2 * kBatchMaxTeam) {
-    // microseconds of a solve by t workgroups: rows at a compute unit's share
-    // of the memory rate, and per batch two workgroup barriers or a meeting
+    // Microseconds of a solve by t workgroups: rows at 25 GB/s, a compute
+    // unit's share of the memory rate, and per batch 2 us for the barriers of a
+    // lone workgroup or 6 for a meeting (4 to 9 where the members arrive
+    // together: BF16, m = 8, us a batch alone / by 8 members, n = 512, b = 64 16 /
+    // 8.3, n = 1024, b = 128 55 / 11, n = 2048, b = 256 206 / 35).
     const auto time_of = [&](int32_t i, int32_t t) {
       const BatchItem& b = table[(size_t)i];
       const double sweeps = 13.8 / -log(b.gamma);
