@@ -497,7 +497,7 @@ bool resident_plan(KParams& p, LaunchShape& shape0, SolveFn* fn, int* blocks) {
   } else if (improves) {
     alone = batch_bytes <= (8 << 10);
   } else {
-    alone = rows <= 32 && batch_bytes < (p.task == kTaskRefine ? 32 << 10 : 64 << 10);
+    alone = rows <= 32 && batch_bytes <= (p.task == kTaskRefine ? 32 << 10 : 64 << 10);
   }
   if (p.n <= kResSoloStates && alone) g = 1;
   // A position's rows are split into a power of two of parts where that

@@ -26,7 +26,7 @@
 // barrier per batch: 8192 x 16, b = 1024 in FP32 96.3 -> 85.3 us (5.6 -> 6.3 TB/s
 // of rows), in FP8 44.9 -> 25.2 us (3.0 -> 5.3 TB/s); 500 x 6, b = 100 26.4 ->
 // 5.3 us.  Modified policy iteration of 6166 x 4 (b = 512, rows of 4-byte
-// alignment) 104 -> 37.6 ms; one sweep of 64 x 4 108 -> 26 us a call; the
+// alignment) 104 -> 37.5 ms; one sweep of 64 x 4 108 -> 26 us a call; the
 // FP64 correction of 4096 x 8 (b = 512) 19.2 -> 8.6 ms.
 
 #pragma once
@@ -434,15 +434,14 @@ struct ResEngine {
 #pragma unroll
         for (int q = 0; q < Rows::kQuads; ++q)
           v[q] = *reinterpret_cast<const v4*>(sh.V + st * Rows::kStep + lane * 4 + q * 256);
-        // What a lane drops must not meet V: 0 times an infinite value is not
-        // 0.  One FP32 row: zeros in the place of V; otherwise the lane skips
-        // the step.  (Each the faster one: 6166 x 4, b = 512, 37.5 ms against
-        // 37.8 with the skip; 500 x 6 3.02 ms against 3.04, FP64 correction of
-        // 4096 x 8 8.6 against 8.7 with zeros.)
-        if constexpr (RC == 1 && Rows::kQuads == 1 && !k64) {
-          const v4 zero = {};
-          v[0] = ok ? v[0] : zero;
-          step(f.x[u], v, acc, 0);
+        // What a lane drops must not meet V: 0 times an infinite value is not 0.
+        // One FP32 row: zeros all the same, and finish_task() takes a sum that
+        // is NaN again; otherwise the lane skips the step.  (Each the faster
+        // one: 6166 x 4, b = 512, 37.4 ms with zeros, 37.8 with the skip, 37.5
+        // with zeros in the place of V; 500 x 6 2.96 ms with the skip, 3.03 with
+        // zeros, the FP64 correction of 4096 x 8 8.6 and 8.7.)
+        if constexpr (kRetake) {
+          step(ok ? f.x[u] : u4{0u, 0u, 0u, 0u}, v, acc, 0);
         } else if (ok) {
 #pragma unroll
           for (int r = 0; r < RC; ++r) step(f.x[r * U + u], v, acc, r);
@@ -462,6 +461,28 @@ struct ResEngine {
     }
   }
 
+  // Where consume() multiplies what it drops by 0, NaN where V is infinite.
+  static constexpr bool kRetake = RC == 1 && Rows::kQuads == 1 && !k64;
+
+  // The task's segment times V, without products of columns that are not its own.
+  __device__ __forceinline__ VT retake(const ResBatch& b, const Task& t) const {
+    const uint8_t* base = table + (size_t)t.at * (size_t)n * T::kBytes;
+    const int s0 = t.seg * b.sps, s1 = min(s0 + b.sps, nsteps);
+    VT acc[kAcc];
+#pragma unroll
+    for (int i = 0; i < kAcc; ++i) acc[i] = 0;
+#pragma unroll 1
+    for (int st = s0; st < s1; ++st) {
+      if (st * 1024 + lane * 16 > n * T::kBytes - 16) continue;
+      const v4 v[1] = {*reinterpret_cast<const v4*>(sh.V + st * Rows::kStep + lane * 4)};
+      step(res_load<NT>(base + st * 1024 + lane * 16), v, acc, 0);
+    }
+    const int jt = (n & ~3) + lane;
+    if (TAIL && s0 < nsteps && s0 + b.sps >= nsteps && jt < n)
+      acc[0] = fma((VT)reinterpret_cast<const float*>(base)[jt], sh.V[jt], acc[0]);
+    return wave_sum_dpp((acc[0] + acc[1 % kAcc]) + (acc[2 % kAcc] + acc[3 % kAcc]));
+  }
+
   // The segment's sums are complete: their share of Q goes to LDS, and the
   // wavefront that completes a unit finds the unit's minimum and publishes it.
   __device__ __forceinline__ void finish_task(const ResBatch& b, int u0, const Task& t,
@@ -476,6 +497,9 @@ struct ResEngine {
         const VT x = wave_sum_dpp(acc[r]);
         sum = lane == r ? x : sum;
       }
+    }
+    if constexpr (kRetake) {
+      if (__builtin_expect(__builtin_isnan(sum), 0)) sum = retake(b, t);
     }
     const double part = T::kType == kF32 ? (double)sum : (double)sum * (double)f.scale;
     const double c = shifted ? __hiloint2double(f.c1, f.c0) : (double)__int_as_float(f.c0);
@@ -1168,7 +1192,11 @@ resident_kernel(KParams kp) {
         bad_entry = true;
       }
   }
-  if (__syncthreads_or(bad_entry)) return;
+  if (TASK == kTaskSweep || TASK == kTaskMPI) {  // (the others read neither)
+    if (__syncthreads_or(bad_entry)) return;
+  } else {
+    __syncthreads();
+  }
 
   long long sweeps = 0, outer = 0, changes_last = -1, recentrings = 0, since = 0;
   double last_dv = NAN, last_err = NAN;

@@ -31,7 +31,7 @@ def handle(n, m, dtype):
 
 
 @pytest.mark.parametrize("dtype,n,m", [("f32", 30, 3), ("f32", 500, 4), ("f32", 2311, 2),
-                                       ("f32", 4099, 2), ("bf16", 504, 3), ("bf16", 2312, 2),
+                                       ("f32", 2312, 2), ("f32", 4099, 2), ("f32", 4100, 2), ("bf16", 504, 3), ("bf16", 2312, 2),
                                        ("fp8", 496, 3), ("fp8", 4112, 1)])
 def test_sweeps(dtype, n, m):
     h = handle(n, m, dtype)
